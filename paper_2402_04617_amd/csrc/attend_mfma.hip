@@ -9,7 +9,7 @@
 //   keys   : the virtual key axis (see StepGeom) in tiles of 64 keys, gathered
 //            straight from the token-ordered store (a selected unit is contiguous)
 //            into LDS by direct global->LDS loads (no staging registers) through
-//            three buffers; optionally split into parts whose partial softmaxes
+//            four buffers, a pair of tiles per barrier; optionally split into parts whose partial softmaxes
 //            are merged afterwards by log-sum-exp.
 // Per wave and key tile:
 //   S^T = K Q^T  : A = K tile rows from LDS, B = the wave's Q rows held in VGPRs.
@@ -42,13 +42,9 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // tile).  No compiler-generated code in these kernels uses M0.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-// Contiguous run: wave-uniform base address plus a per-lane 32-bit byte offset.
-__device__ __forceinline__ void lds_load_run(uint32_t lds, const void* base, uint32_t off) {
+// Wave-uniform base address plus a per-lane 32-bit byte offset.
+__device__ __forceinline__ void lds_load(uint32_t lds, const void* base, uint32_t off) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "m0");
-}
-// Gather: a full per-lane address.
-__device__ __forceinline__ void lds_load_lane(uint32_t lds, const void* p) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(p) : "m0");
 }
 #pragma clang diagnostic pop
 
@@ -78,19 +74,21 @@ __device__ __forceinline__ int swz(int r) {
 template <int D>
 __device__ __forceinline__ int tile_off(int r, int g) { return r * D + 8 * (g ^ swz<D>(r)); }
 
-constexpr int NBUF = 3;         // K and V tile buffers
+constexpr int NBUF = 4;         // K and V tile buffers: a pair of tiles in use, the next pair in flight
 constexpr int kMaskCost = 6;  // cost of a masked tile, in quarters of a plain tile (measured ~1.5x)
 constexpr int kSelTiles4 = 5;  // the in-prologue unit selection, in quarters of a plain tile
 constexpr int kSelTiles4Long = 16;  // the same for rows of more than kFusedSelectShort units
-constexpr int kRunTable = 1024;  // run starts kept in LDS for the part's tiles
+constexpr int kRowTable = 4096;  // key-group positions kept in LDS (512 tiles of 8-key groups, 64 of single keys)
 constexpr int kSelLds = 1024;    // lookup entries kept in LDS
 static_assert(kFusedSelectMaxK <= kSelLds, "a selected lookup row fits in LDS");
+
+constexpr uint32_t kNoRow = 0xFFFFFFFFu;
 
 template <int D>
 struct Smem {
   bf16_t k[NBUF][KB * D];
   bf16_t v[NBUF][KB * D];
-  int64_t runs[kRunTable];  // run start of tile t_begin + i (see tile_run_start)
+  uint32_t rows[kRowTable];  // store position of each key group of a window of tiles (kNoRow: skipped entry)
   int32_t sidx[kSelLds];    // the lookup row (its first kSelLds entries)
   uint8_t kvalid[NBUF][KB];
 };
@@ -125,7 +123,6 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   constexpr int RPI = 64 / CH;                // tile rows per 1 KB load instruction
   constexpr int NI = KB * D * 2 / (NWAVE * 1024);  // load instructions per wave per tile (K or V)
   static_assert(NI * NWAVE * RPI == KB, "tile rows covered exactly once");
-  static_assert(2 * NI <= KSTEPS, "one load per chunk of the MFMA phase");
   __shared__ __attribute__((aligned(256))) Smem<D> sm;
 
   const int G = a.n_q_heads / a.n_kv_heads;
@@ -163,43 +160,39 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
     rpart = part - parts_mem;
     rparts = a.parts - parts_mem;
   }
-  // The parts split the range by cost rather than by tile count: a tile holding
-  // current-token keys (the causal diagonal, masked) costs kMaskCost/4 of a plain
-  // tile, so the part that takes the diagonal takes fewer tiles and all parts end
-  // together.
+  // The parts split the tiles this row tile's queries see by cost rather than by
+  // count, so that they end together: a masked tile (the causal diagonal) costs
+  // kMaskCost/4 plain tiles, and with the selection inside (SEL) the parts that
+  // read unit keys also select the units (see below), kSelTiles4/4 tiles of work
+  // each: the tiles up to the end of the units are charged that work spread over
+  // them, for the share of the parts expected to fall there.
   const int v_x0 = geo.n_virtual - geo.n_q;  // first current-token key
-  auto part_bound = [&](int pp) -> int {  // first tile of part pp of rparts
-    const int a_x = min(max(v_x0 / KB, rt0), rt1);
-    if constexpr (!SEL) {
-      const int64_t c_plain = 4LL * (a_x - rt0);
-      const int64_t c_all = c_plain + (int64_t)kMaskCost * (rt1 - a_x);
-      const int64_t c = c_all * pp / rparts;
-      if (c <= c_plain) return rt0 + (int)((c + 3) / 4);
-      return a_x + (int)((c - c_plain + kMaskCost - 1) / kMaskCost);
-    }
-    // The parts that read unit keys also select the units (see below), about
-    // kSelTiles tiles of work each.  The tiles up to the end of the units are
-    // charged that work spread over them, for the share of the parts expected to
-    // fall there (costs in 1/64 of a plain tile).
-    const int u_end = (geo.n_init + geo.n_sel * geo.block_size + KB - 1) / KB;
-    const int s_end = min(max(u_end, rt0), a_x);
+  const int qi_min = min(R - 1, rt * ROWS_WG) / G, qi_max = (min(R, (rt + 1) * ROWS_WG) - 1) / G;
+  const int vis_end = mem_part ? mem_len : v_x0 + qi_min + 1;  // every row of the tile sees the keys below
+  rt1 = min(rt1, (v_x0 + qi_max) / KB + 1);                    // later tiles are fully causal-masked
+  auto part_bound = [&](int pp) -> int {  // first tile of part pp of rparts (costs in 1/64 of a plain tile)
+    const int a_m = min(max(vis_end / KB, rt0), rt1);  // first masked tile
     constexpr int64_t kPlain = 64, kMask = 16 * kMaskCost;
-    constexpr int64_t kSel4 = SEL > 2 ? kSelTiles4Long : kSelTiles4;
-    const int64_t kSel = kPlain + (kPlain * kSel4 * rparts) / (4 * max(1, rt1 - rt0));
+    int s_end = rt0;
+    int64_t kSel = kPlain;
+    if constexpr (SEL > 0) {
+      const int u_end = (geo.n_init + geo.n_sel * geo.block_size + KB - 1) / KB;
+      constexpr int64_t kSel4 = SEL > 2 ? kSelTiles4Long : kSelTiles4;
+      if (geo.n_sel > 0 && geo.n_sel < geo.n_units) {
+        s_end = min(max(u_end, rt0), a_m);
+        kSel += (kPlain * kSel4 * rparts) / (4 * max(1, rt1 - rt0));
+      }
+    }
     const int64_t c_sel = kSel * (s_end - rt0);
-    const int64_t c_plain = c_sel + kPlain * (a_x - s_end);
-    const int64_t c_all = c_plain + kMask * (rt1 - a_x);
+    const int64_t c_plain = c_sel + kPlain * (a_m - s_end);
+    const int64_t c_all = c_plain + kMask * (rt1 - a_m);
     const int64_t c = c_all * pp / rparts;
     if (c <= c_sel) return rt0 + (int)((c + kSel - 1) / kSel);
     if (c <= c_plain) return s_end + (int)((c - c_sel + kPlain - 1) / kPlain);
-    return a_x + (int)((c - c_plain + kMask - 1) / kMask);
+    return a_m + (int)((c - c_plain + kMask - 1) / kMask);
   };
   const int t_begin = part_bound(rpart);
-  int t_end = part_bound(rpart + 1);
-  {
-    const int i_max = (min(R, (rt + 1) * ROWS_WG) - 1) / G;
-    t_end = min(t_end, (v_x0 + i_max) / KB + 1);  // tiles past this are fully causal-masked
-  }
+  const int t_end = part_bound(rpart + 1);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -207,6 +200,10 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   const int n = lane & 31, gsel = lane >> 5;
   const int row = rt * ROWS_WG + wave * 32 + n;
   const bool row_ok = row < R;
+  // A wave whose 32 rows all lie past the last query (a short or ragged chunk)
+  // computes nothing: it only loads its rows of the tiles and keeps the barriers,
+  // which leaves its SIMD's matrix core and the power budget to the others.
+  const bool active = rt * ROWS_WG + wave * 32 < R;
   const int qi = row_ok ? row / G : 0;
   // last virtual key this row may see: causal within X (which also excludes the
   // ragged end), or for a memory part of the remap the last memory key
@@ -306,105 +303,89 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
 
   // Direct loads: instruction j of wave w fills LDS granules [(NI*w + j)*64, +64)
   // of the tile, lane l writing granule slot l; that slot belongs to tile row
-  // r_j = (NI*w + j)*RPI + l / CH and holds its global granule (l % CH) ^ swz(r_j).
-  // Under the swizzle r_j = r_0 + RPI*j and granule_j = granule_0 ^ XJ*j.
-  constexpr int XJ = D == 128 ? 1 : 0;
-  const int lrow0 = NI * wave * RPI + lane / CH;
-  const int lgran0 = (lane % CH) ^ swz<D>(lrow0);
+  // r_j = r_0 + RPI*j, r_0 = 8*w + l / CH, and holds its global granule
+  // (l % CH) ^ swz(r_j); a wave's loads cover the eight rows [8w, 8w + 8).
+  static_assert(NI * RPI == 8, "a wave loads eight rows of a tile");
+  const int lrow0 = 8 * wave + lane / CH;
 
-  // A tile inside one segment (I, one selected unit, or the L+X run) maps to 64
-  // consecutive store positions: the common case, gathered with no per-key work.
-  // Returns that first position (uniform across the workgroup) or -1.
-  auto tile_run_start = [&](int tile) -> int64_t {
-    const int v0 = tile * KB;
-    if (has_invalid || v0 + KB > geo.n_virtual) return -1;
-    if (v0 + KB <= geo.n_init) return v0;
-    if (v0 < geo.n_init) return -1;
-    const int w = v0 - geo.n_init;
-    const int sel_len = geo.n_sel * geo.block_size;
-    if (w >= sel_len) return geo.local_begin + (w - sel_len);
-    if (w + KB > sel_len) return -1;
-    const int u = w / geo.block_size;
-    if ((w + KB - 1) / geo.block_size != u) return -1;
-    const int bu = u < kSelLds ? sm.sidx[u] : idx_row[u];
-    return (int64_t)geo.unit_base + (int64_t)bu * geo.block_size + (w - u * geo.block_size);
+  // Store positions of the keys.  The virtual axis is cut into groups of 8 keys
+  // when no group crosses a boundary between I, the units and the local run
+  // (l_I and l_bs multiples of 8), else into single keys; a table in LDS holds the
+  // position of every group's first key for a window of tiles.  A lane's load
+  // offset is then one table read and three integer operations whatever the
+  // tile holds -- no branch, no division in the tile loop.  (With per-tile run
+  // starts, a branch to a per-key path and 64-bit arithmetic the bookkeeping
+  // between the matrix phases took 870 of an iteration's 3,600 cycles.)
+  const int gshift = ((geo.n_init | geo.block_size) & 7) == 0 ? 3 : 0;
+  const int tile_groups = KB >> gshift;
+  const int window = kRowTable / tile_groups;  // tiles in the table
+  // The last position of the axis is the store's last written row: an offset past
+  // it (a ragged end, a tile past the axis) reads that row instead, which the
+  // causal bound masks.
+  const uint32_t last_row = (uint32_t)(geo.past_len + geo.n_q - 1);
+  auto group_row = [&](int v) -> uint32_t {
+    int64_t pos = v;
+    if (v >= geo.n_init) {
+      const int w = v - geo.n_init;
+      const int sel_len = geo.n_sel * geo.block_size;
+      if (w >= sel_len) {
+        pos = geo.local_begin + (w - sel_len);
+      } else {
+        const int u = w / geo.block_size;
+        const int bu = u < kSelLds ? sm.sidx[u] : idx_row[u];
+        if (bu < 0 || bu >= geo.n_units) return kNoRow;
+        pos = (int64_t)geo.unit_base + (int64_t)bu * geo.block_size + (w - u * geo.block_size);
+      }
+    }
+    return (uint32_t)min(pos, (int64_t)last_row);
   };
-  // Store position of virtual key v (-1: skipped unit entry), with the lookup
-  // entry read from LDS: on the per-key path of tiles that span several runs a
-  // global read would wait behind the tile loads in flight.
-  auto vpos = [&](int v) -> int64_t {
-    if (v < geo.n_init) return v;
-    const int w = v - geo.n_init;
-    const int sel_len = geo.n_sel * geo.block_size;
-    if (w >= sel_len) return geo.local_begin + (w - sel_len);
-    const int u = w / geo.block_size;
-    const int bu = u < kSelLds ? sm.sidx[u] : idx_row[u];
-    if (bu < 0 || bu >= geo.n_units) return -1;
-    return (int64_t)geo.unit_base + (int64_t)bu * geo.block_size + (w - u * geo.block_size);
+  int w0 = t_begin;  // first tile of the table's window
+  auto fill_rows = [&](int first) {
+    w0 = first;
+    const int n = min(kRowTable, (t_end + 7 - first) * tile_groups);
+    for (int i = tid; i < n; i += 64 * NWAVE) sm.rows[i] = group_row(first * KB + (i << gshift));
   };
-  auto uniform64 = [](int64_t x) -> int64_t {
-    return ((int64_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
-           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  // this lane's table entry of a tile, and its row within the group
+  const uint32_t lds_rows = (uint32_t)(uintptr_t)(INFLLM_LDS uint32_t*)sm.rows;
+  const uint32_t gr_mask = (1u << gshift) - 1u;
+  // Byte offsets (from the slice base) of this lane's loads of tile `tile`.  The
+  // host guarantees that one (sequence, kv head) slice of the store spans less than
+  // 4 GiB.  A skipped unit entry reads row 0 -- always written -- and is masked.
+  struct TileOff {
+    uint32_t o[NI];
+  };
+  auto row_read = [&](int tile, uint32_t (&e)[NI]) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const uint32_t at = lds_rows + 4u * ((uint32_t)(lrow0 + RPI * j) >> gshift);
+      e[j] = *(const INFLLM_LDS uint32_t*)(uintptr_t)(at + 4u * (uint32_t)((tile - w0) * tile_groups));
+    }
+  };
+  auto row_off = [&](const uint32_t (&e)[NI], TileOff& f) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const uint32_t r = (uint32_t)(lrow0 + RPI * j);
+      const uint32_t gran = (uint32_t)(lane % CH) ^ (uint32_t)swz<D>(lrow0 + RPI * j);
+      const uint32_t base = has_invalid && e[j] == kNoRow ? 0u : e[j];
+      f.o[j] = (min(base + (r & gr_mask), last_row) * (2u * D)) | (16u * gran);
+    }
   };
 
-  // Byte offsets of this wave's 1 KB slices in the LDS tiles, and the per-lane
-  // byte offset of the granule each lane fetches within a contiguous run.
+  // Byte offsets of this wave's 1 KB slices in the LDS tiles.
   const uint32_t lds_k0 = (uint32_t)(uintptr_t)(INFLLM_LDS bf16_t*)sm.k[0];
   const uint32_t lds_v0 = (uint32_t)(uintptr_t)(INFLLM_LDS bf16_t*)sm.v[0];
   const uint32_t lds_k = lds_k0 + NI * wave * 1024;
   const uint32_t lds_v = lds_v0 + NI * wave * 1024;
   constexpr uint32_t kTileBytes = KB * D * 2;
-  // byte offset of instruction j's granule within a contiguous run:
-  // (run_off0 ^ 16*XJ*j) + 1024*j
-  const uint32_t run_off0 = (uint32_t)(lrow0 * D + 8 * lgran0) * 2u;
-
-  // Direct loads of tile `tile` (run start `run0`) into buffer `buf` of K or of
-  // V.  A key that is not part of the context (ragged end, skipped unit entry)
-  // reads position 0 -- always written -- and is masked to -inf before the
-  // softmax (the ragged end by the causal bound, a skipped entry by kvalid, which
-  // the K load records), so its K/V never contribute.
-  auto issue = [&](int tile, int64_t run0, int buf, auto is_k) {
-    constexpr bool IS_K = decltype(is_k)::value;
-    const uint32_t ld = (IS_K ? lds_k : lds_v) + buf * kTileBytes;
-    const bf16_t* base = IS_K ? kbase : vbase;
-    if (run0 >= 0) {
-      const bf16_t* src = base + run0 * D;
-      const uint32_t ro = opaque_v(run_off0);
+  // load j of a tile into buffer `buf` of K or V
+  auto load_k = [&](int buf, const TileOff& f, int j) { lds_load(lds_k + buf * kTileBytes + j * 1024, kbase, f.o[j]); };
+  auto load_v = [&](int buf, const TileOff& f, int j) { lds_load(lds_v + buf * kTileBytes + j * 1024, vbase, f.o[j]); };
+  // with skipped unit entries: the validity of the keys this wave loads into K buffer `buf`
+  auto note_valid = [&](int buf, const uint32_t (&e)[NI]) {
+    if (has_invalid) {
 #pragma unroll
-      for (int j = 0; j < NI; ++j) lds_load_run(ld + j * 1024, src + 512 * j, ro ^ (16u * XJ * j));
-    } else {
-#pragma unroll
-      for (int j = 0; j < NI; ++j) {
-        const int r = lrow0 + RPI * j;
-        const int v = tile * KB + r;
-        int64_t pos = v < geo.n_virtual ? vpos(v) : -1;
-        if (IS_K && lane % CH == 0) sm.kvalid[buf][r] = pos >= 0;
-        pos = pos >= 0 ? pos : 0;
-        lds_load_lane(ld + j * 1024, base + pos * D + 8 * (lgran0 ^ (XJ * j)));
-      }
-    }
-  };
-  // The same loads split in two: per-lane byte offsets from the store base
-  // (formed at the top of an iteration; per-key gather on the uncommon path) and
-  // the loads themselves, issued one per chunk of the MFMA phase so that the
-  // waves of the workgroup do not queue a burst of them after the barrier.  The
-  // host guarantees that one (sequence, kv head) slice of the store spans less
-  // than 4 GiB, so the offsets fit 32 bits.
-  auto load_offsets = [&](int tile, int64_t run0, int buf, bool is_k, uint32_t (&off)[NI]) {
-    if (run0 >= 0) {
-      const uint32_t ro = opaque_v(run_off0) + (uint32_t)run0 * (2u * D);
-#pragma unroll
-      for (int j = 0; j < NI; ++j) off[j] = (ro ^ (16u * XJ * j)) + 1024u * j;
-    } else {
-#pragma unroll
-      for (int j = 0; j < NI; ++j) {
-        const int r = lrow0 + RPI * j;
-        const int v = tile * KB + r;
-        int64_t pos = v < geo.n_virtual ? vpos(v) : -1;
-        if (is_k && lane % CH == 0) sm.kvalid[buf][r] = pos >= 0;
-        pos = pos >= 0 ? pos : 0;
-        off[j] = (uint32_t)pos * (2u * D) + 16u * (lgran0 ^ (XJ * j));
-      }
+      for (int j = 0; j < NI; ++j)
+        if (lane % CH == 0) sm.kvalid[buf][lrow0 + RPI * j] = e[j] != kNoRow;
     }
   };
 
@@ -523,14 +504,15 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
     return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c2;  // c2 > 0
   };
   // Lazy running max.  P is formed against the running max m_run without first
-  // taking the tile's own maximum; a row whose half-tile sum of P exceeds kLazy
+  // taking the tile's own maximum; a row whose sum of P over a tile exceeds kLazy
   // (2^16: P stays far inside the float and bf16 range) has met keys well above
   // m_run, and only then is the tile's maximum taken and the row rescaled (a rare
   // path; the decision is wave-uniform, and both lane halves of a row share
   // m_run).  While a row has seen no visible key (m_run = -inf) any nonzero P
   // takes that path, so the first visible tile sets m_run.
   constexpr float kLazy = 65536.f;
-  auto lazy_bound = [&]() { return m_run == -__builtin_inff() ? 0.f : kLazy; };
+  float lazy_bound = 0.f;  // 0 while m_run = -inf
+  float neg_m = 0.f;       // -m_run, 0 while m_run = -inf
   auto force_max = [&](float mx) {
     const float m_new = fmaxf(m_run, mx);
     const float alpha = (m_new == -__builtin_inff()) ? 1.f : fast_exp2(m_run - m_new);
@@ -540,6 +522,8 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
 #pragma unroll
       for (int j = 0; j < 16; ++j) oacc[db][j] *= alpha;
     m_run = m_new;
+    neg_m = (m_new == -__builtin_inff()) ? 0.f : -m_new;
+    lazy_bound = (m_new == -__builtin_inff()) ? 0.f : kLazy;
   };
   // Tile t's contribution to the unit masses (MASS): for a tile of the looked-up
   // units (whole tiles: l_I and l_bs are multiples of the tile), the row's sum of
@@ -559,22 +543,22 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   // Two P values as a bf16 pair (one v_cvt_pk_bf16_f32), added unrounded to the
   // two running row sums (the normaliser keeps float32 precision; rounding only
   // the PV operand moves O by at most 2^-9 relative).
-  auto p_pair = [&](float z0, float z1, float nm, float (&acc)[2]) -> uint32_t {
+  auto p_pair = [&](float z0, float z1, float nm, float (&acc)[2], bool first) -> uint32_t {
     const float e0 = fast_exp2(__builtin_fmaf(z0, c2, nm));
     const float e1 = fast_exp2(__builtin_fmaf(z1, c2, nm));
-    acc[0] += e0;
-    acc[1] += e1;
+    acc[0] = first ? e0 : acc[0] + e0;
+    acc[1] = first ? e1 : acc[1] + e1;
     bf16x2 pr;
     pr[0] = (__bf16)e0;
     pr[1] = (__bf16)e1;
-    return __builtin_bit_cast(uint32_t, pr);
+    // (opaque: the conversion stays in the matrix phase it is written in)
+    return opaque_v(__builtin_bit_cast(uint32_t, pr));
   };
   // One 16-key half of P = exp2(S*c2 - m_run) as the bf16 operand pair, and its row sum.
   auto half_p = [&](const f32x16& sh, u32x4 (&ph)[2]) {
-    const float nm = (m_run == -__builtin_inff()) ? 0.f : -m_run;
-    float ps[2] = {0.f, 0.f};
+    float ps[2];
 #pragma unroll
-    for (int w = 0; w < 8; ++w) ph[w >> 2][w & 3] = p_pair(sh[2 * w], sh[2 * w + 1], nm, ps);
+    for (int w = 0; w < 8; ++w) ph[w >> 2][w & 3] = p_pair(sh[2 * w], sh[2 * w + 1], neg_m, ps, w == 0);
     return ps[0] + ps[1];
   };
   auto as_bf16x8 = [](const u32x4& w) { return __builtin_bit_cast(bf16x8, w); };
@@ -597,65 +581,60 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   };
 
   // ---- software pipeline over the part's tiles ---------------------------------
-  // Tile x lives in K buffer and V buffer (x - t_begin) % 3.  Iteration t runs
-  // PV(t) and QK(t+1): the matrix cores work on QK(t+1) while the vector ALUs
-  // form the keys [32, 64) half of P(t), and on PV(t) while they take the mask
-  // and max of tile t+1 and form the keys [0, 32) half of P(t+1) with the
-  // running max (redone in the rare iteration whose tile raises the max past the
-  // lazy-rescale threshold), which balances the vector work over both phases.  Loads are
-  // issued two iterations ahead, K three tiles ahead and V two tiles ahead, so
-  // each buffer is refilled only after the barrier that retires its last readers:
-  //   top of iteration t: wait for K(t+1), V(t) (issued two iterations ago; the
-  //   2*NI loads of the previous iteration may stay in flight), barrier; issue
-  //   K(t+3) into the K buffer of tile t (QK(t) ran in iteration t-1) and V(t+2)
-  //   into the V buffer of tile t-1.
-  // Every iteration issues exactly 2*NI loads per wave, which keeps the wait
-  // count constant: a tile past the part's end is simply loaded too (a tile past
-  // the key axis reads position 0), into a buffer nobody reads.  Run starts are
-  // looked up at the end of an iteration, so their scalar loads complete under
-  // the barrier.
-  // Tiles wholly before X need no mask unless skipped unit entries exist.
-  const int t_plain = has_invalid ? t_begin : max(t_begin, min(t_end, (mem_part ? mem_len : v_x0) / KB));
-  int64_t run_k = -1, run_v = -1;  // run starts of the next K and V loads: tiles t+3, t+2
-  // Run starts of the part's tiles, computed once by all lanes into LDS; the
-  // per-iteration lookup is then an LDS read (a global read here would wait
-  // behind the tile loads in flight).  Tiles past the table compute directly.
-  const int n_table = min(kRunTable, t_end + 4 - t_begin);
-  for (int i = tid; i < n_table; i += 64 * NWAVE) sm.runs[i] = tile_run_start(t_begin + i);
-  // early half of a lookup: the LDS read (or -2 when the tile is past the table)
-  auto run_read = [&](int tile) -> int64_t {
-    const int i = tile - t_begin;
-    return i < n_table ? sm.runs[i] : -2;
-  };
-  auto run_finish = [&](int tile, int64_t r) -> int64_t { return uniform64(r != -2 ? r : tile_run_start(tile)); };
+  // Tile x lives in K buffer and V buffer (x - t_begin) % 4.  A step of tile t runs
+  // QK(t+1) and PV(t): the matrix cores work on QK(t+1) while the vector ALUs form
+  // the keys [32, 64) half of P(t), and on PV(t) while they take the mask of tile
+  // t+1 and form the keys [0, 32) half of P(t+1) with the running max; both halves
+  // of a tile are checked against the lazy bound once, before PV(t).  Everything
+  // else a step needs (load offsets, conversions, the first V^T fragments) is
+  // formed inside those two phases, so that the matrix cores idle only where the
+  // waves meet: one barrier per PAIR of tiles t, t+1.  At its top every load of the
+  // previous pair has landed (K(t+1), K(t+2), V(t), V(t+1)); the pair's first phase
+  // issues K(t+3), K(t+4), V(t+2), V(t+3) into the buffers whose readers the
+  // barrier retired, nearly two tiles of work ahead of their use.  A tile past the
+  // part's end is simply loaded too, into a buffer nobody reads.
+  // What bounds it: power.  With three buffers, a barrier per tile, per-tile run
+  // starts and two lazy checks an iteration took 3,600 cycles (2,048 of matrix work
+  // for the two waves of a SIMD); it takes 3,200 now, at a clock that falls as the
+  // loop gets denser (1.9 GHz in a 128K step; the loop alone runs 2,770 cycles at
+  // 1.62 GHz, 1.7 us per tile, and 2.18 GHz on zeros).  Step at 1M (2,048 queries,
+  // 162 tiles) 352 -> 333 us, at 128K 91.6 -> 90.3 us; 24 queries of four
+  // sequences, five of eight waves idle, 65.6 -> 61.3 us.
+  // Tiles whose keys every row of the workgroup sees need no mask unless skipped
+  // unit entries exist.
+  const int t_plain = has_invalid ? t_begin : max(t_begin, min(t_end, vis_end / KB));
   f32x16 sA[2], sB[2];
-  // p0: the keys [0, 32) half of P(t), formed in the previous iteration's phase 2
-  // (or the prologue), and l_pend its row sum, added to l_run once the other half
-  // of the tile has passed its lazy-max check; replaced here by that half of P(t+1).
+  // p0: the keys [0, 32) half of P(t), formed in the previous step's second phase
+  // (or the prologue), and l_pend its row sum, added to l_run once the tile has
+  // passed its lazy-max check; replaced there by that half of P(t+1).
   u32x4 p0[2];
   float l_pend = 0.f;
-  auto iteration = [&](int t, f32x16 (&cur)[2], f32x16 (&nxt)[2], auto mask_next) {
-    const int bc = (t - t_begin) % NBUF;
-    const int bn = bc == NBUF - 1 ? 0 : bc + 1, bp = bc == 0 ? NBUF - 1 : bc - 1;
-    publish_barrier<2 * NI>();
-    uint32_t off_k[NI], off_v[NI];
-    load_offsets(t + 3, run_k, bc, true, off_k);
-    load_offsets(t + 2, run_v, bp, false, off_v);
-    const uint32_t ld_k = lds_k + bc * kTileBytes, ld_v = lds_v + bp * kTileBytes;
-    const int64_t run_next = run_read(t + 4);  // consumed after phase 2
-
-    // Phases 1 and 2 run at raised wave priority (s_setprio 1), the barrier,
-    // address and bookkeeping at normal priority: a wave in its MFMA phases
-    // wins the issue slots of its SIMD over a wave doing bookkeeping (measured a
-    // few percent faster than uniform priority).
-    __builtin_amdgcn_s_setprio(1);
-    // Phase 1: QK(t+1) on the matrix cores, the keys [32, 64) half of P(t) on the
-    // vector ALUs.  Chunk s issues the K fragment reads of k-step s+1, the two
-    // MFMAs of k-step s and EPC elements of that half of P(t); scheduling fences
-    // keep that interleave.
-    float neg_m = (m_run == -__builtin_inff()) ? 0.f : -m_run;
+  // load offsets of tiles t+2, t+3, t+4 of the pair at hand, and the table entries
+  // of K(t+3), K(t+4) (kept for their validity flags)
+  TileOff off2, off3, off4;
+  uint32_t e3[NI], e4[NI];
+  // the offsets of the pair after the one whose second tile is t, in one go
+  auto next_offsets = [&](int t) {
+    off2 = off4;
+    row_read(t + 4, e3);
+    row_read(t + 5, e4);
+    row_off(e3, off3);
+    row_off(e4, off4);
+  };
+  // One tile's step: FIRST of the pair (issues the pair's loads) or second (forms
+  // the next pair's load offsets); NEXT_MASK: tile t+1 is masked.
+  auto tile_step = [&](int t, f32x16 (&cur)[2], f32x16 (&nxt)[2], auto first_of_pair, auto next_mask) {
+    constexpr bool FIRST = decltype(first_of_pair)::value;
+    constexpr bool MASK = decltype(next_mask)::value;
+    const int bc = (t - t_begin) % NBUF, bn = (bc + 1) % NBUF;
+    // Phase 1.  Chunk s issues the K fragment reads of k-step s+1, the two MFMAs of
+    // k-step s and EPC elements of the second half of P(t); scheduling fences keep
+    // that interleave.
     u32x4 w1[2];
-    float ps1[2] = {0.f, 0.f};  // two partial row sums (shorter dependency chains)
+    float ps1[2];  // two partial row sums (shorter dependency chains)
+    bf16x8 va[DBLK];
+    const uint32_t vaddr = vaddr_of(bc);
+    auto vfrag = [&](int db, int j) { return vfrag_at(vaddr, db, j); };
     {
       const uint32_t ka = kaddr_of(bn);
       auto kfrag = [&](int kb, int s) { return kfrag_at(ka, kb, s); };
@@ -664,11 +643,15 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
       a1[0] = kfrag(1, 0);
       constexpr int EPC = 16 / KSTEPS;  // elements of P(t)'s keys [32, 64) half per chunk
       static_assert(EPC % 2 == 0, "P elements are formed in bf16 pairs");
+      static_assert(4 * NI <= KSTEPS, "one load per chunk");
 #pragma unroll
       for (int s = 0; s < KSTEPS; ++s) {
         if (s + 1 < KSTEPS) {
           a0[(s + 1) & 1] = kfrag(0, s + 1);
           a1[(s + 1) & 1] = kfrag(1, s + 1);
+        } else {
+#pragma unroll
+          for (int db = 0; db < DBLK; ++db) va[db] = vfrag(db, 0);
         }
         if (s == 0) {
           const f32x16 zero = {};
@@ -678,39 +661,39 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
           nxt[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[s & 1], qreg[s], nxt[0], 0, 0, 0);
           nxt[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[s & 1], qreg[s], nxt[1], 0, 0, 0);
         }
-        // the s-th of this wave's 2*NI loads of K(t+3) and V(t+2)
-        if (s < NI) lds_load_run(ld_k + s * 1024, kbase, off_k[s]);
-        else if (s < 2 * NI) lds_load_run(ld_v + (s - NI) * 1024, vbase, off_v[s - NI]);
+        if constexpr (FIRST) {
+          // the s-th of this wave's 4*NI loads: K(t+3), V(t+2), K(t+4), V(t+3)
+          const int i = s / NI, j = s % NI;
+          if (i == 0) load_k((bc + 3) % NBUF, off3, j);
+          else if (i == 1) load_v((bc + 2) % NBUF, off2, j);
+          else if (i == 2) load_k(bc, off4, j);
+          else if (i == 3) load_v((bc + 3) % NBUF, off3, j);
+        }
 #pragma unroll
         for (int i = 0; i < EPC; i += 2) {
           const int w = (EPC * s + i) >> 1;  // bf16 pair index within the half
-          w1[w >> 2][w & 3] = p_pair(cur[1][2 * w], cur[1][2 * w + 1], neg_m, ps1);
+          w1[w >> 2][w & 3] = p_pair(cur[1][2 * w], cur[1][2 * w + 1], neg_m, ps1, w == 0);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    float psum1 = ps1[0] + ps1[1];
-    // lazy-max check of that half before it reaches the matrix cores: on the rare
-    // row that exceeds the bound, rescale to the tile's maximum and redo both halves
-    if (__ballot(psum1 > lazy_bound())) {
+    float l_tile = l_pend + (ps1[0] + ps1[1]);
+    // lazy-max check before the tile reaches the matrix cores: on the rare row that
+    // exceeds the bound, rescale to the tile's maximum and redo both halves
+    if (__ballot(l_tile > lazy_bound)) {
       force_max(tile_max(cur));
-      l_pend = half_p(cur[0], p0);
-      psum1 = half_p(cur[1], w1);
-      neg_m = (m_run == -__builtin_inff()) ? 0.f : -m_run;
+      l_tile = half_p(cur[0], p0);
+      l_tile += half_p(cur[1], w1);
     }
-    l_run += l_pend + psum1;
-    if constexpr (MASS) mass_tile(t, l_pend + psum1);
+    l_run += l_tile;
+    if constexpr (MASS) mass_tile(t, l_tile);
 
     // Phase 2: PV(t) on the matrix cores; on the vector ALUs the mask of tile t+1
     // (one 8-element group of its 32 accumulator elements per step) and, four
-    // elements per step, the keys [0, 32) half of P(t+1) against the running max
-    // (checked after the phase).
+    // elements per step, the keys [0, 32) half of P(t+1) against the running max.
     u32x4 q0[2];
-    float ps0[2] = {0.f, 0.f};
+    float ps0[2];
     {
-      constexpr bool MASK = decltype(mask_next)::value;
-      const uint32_t vaddr = vaddr_of(bc);
-      auto vfrag = [&](int db, int j) { return vfrag_at(vaddr, db, j); };
       const int lim = vlim - (t + 1) * KB - 4 * gsel;  // mask bound of tile t+1
       uint32_t kv[4][2];
       if (MASK && has_invalid) {
@@ -720,11 +703,21 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
           for (int j4 = 0; j4 < 4; ++j4)
             kv[j4][kb] = *(const uint32_t*)&sm.kvalid[bn][32 * kb + 8 * j4 + 4 * gsel];
       }
-      bf16x8 va[DBLK];
-#pragma unroll
-      for (int db = 0; db < DBLK; ++db) va[db] = vfrag(db, 0);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
+        if constexpr (!FIRST) {
+          // the next pair's load offsets: V(t+3) .. of this pair's last K tile, then
+          // the table entries of the two K tiles after it
+          if (j == 0) {
+            off2 = off4;
+            row_read(t + 4, e3);
+            row_read(t + 5, e4);
+          } else if (j == 2) {
+            row_off(e3, off3);
+          } else if (j == 3) {
+            row_off(e4, off4);
+          }
+        }
 #pragma unroll
         for (int db = 0; db < DBLK; ++db) {
           oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[db], as_bf16x8(j < 2 ? p0[j & 1] : w1[j & 1]),
@@ -755,21 +748,33 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
           const int w = 2 * j + i;
-          q0[w >> 2][w & 3] = p_pair(nxt[0][2 * w], nxt[0][2 * w + 1], neg_m, ps0);
+          q0[w >> 2][w & 3] = p_pair(nxt[0][2 * w], nxt[0][2 * w + 1], neg_m, ps0, w == 0);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    __builtin_amdgcn_s_setprio(0);
     p0[0] = q0[0];
     p0[1] = q0[1];
     l_pend = ps0[0] + ps0[1];
-    if (__ballot(l_pend > lazy_bound())) {
-      force_max(tile_max(nxt));
-      l_pend = half_p(nxt[0], p0);
+  };
+  // The top of a pair: its tiles' loads have landed, and the buffers of the
+  // previous pair are free.
+  auto pair_top = [&](int t) {
+    __builtin_amdgcn_s_setprio(0);
+    publish_barrier<0>();
+    if (has_invalid) {
+      note_valid((t - t_begin + 3) % NBUF, e3);
+      note_valid((t - t_begin) % NBUF, e4);
     }
-    run_v = run_k;
-    run_k = run_finish(t + 4, run_next);
+    if (t + 6 >= w0 + window) {
+      // the second step reads the table for tiles t+5, t+6: move the window there
+      // (its readers are past the barrier)
+      fill_rows(t + 5);
+      publish_barrier<0>();
+    }
+    // The matrix phases run at raised wave priority: a wave in its MFMA phases
+    // wins the issue slots of its SIMD over a wave doing bookkeeping.
+    __builtin_amdgcn_s_setprio(1);
   };
   auto copy_state = [](f32x16 (&dst)[2], const f32x16 (&src)[2]) {
     dst[0] = src[0];
@@ -777,19 +782,52 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   };
 
   if (t_begin < t_end) {
-    // K(t0), V(t0), K(t0+1) | V(t0+1), K(t0+2): the last two groups play the
-    // loads of "the previous iteration" for the first iteration's wait.
-    const int64_t r0 = uniform64(tile_run_start(t_begin));
-    const int64_t r1 = uniform64(tile_run_start(t_begin + 1));
-    const int64_t r2 = uniform64(tile_run_start(t_begin + 2));
-    issue(t_begin, r0, 0, std::true_type{});
-    issue(t_begin, r0, 0, std::false_type{});
-    issue(t_begin + 1, r1, 1, std::true_type{});
-    issue(t_begin + 1, r1, 1, std::false_type{});
-    issue(t_begin + 2, r2, 2, std::true_type{});
-    run_v = r2;
-    run_k = uniform64(tile_run_start(t_begin + 3));
+    fill_rows(t_begin);
+    __syncthreads();
+    TileOff off0, off1;
+    {
+      uint32_t e0[NI], e1[NI], e2[NI];
+      row_read(t_begin, e0);
+      row_read(t_begin + 1, e1);
+      row_read(t_begin + 2, e2);
+      row_read(t_begin + 3, e3);
+      row_read(t_begin + 4, e4);
+      row_off(e0, off0);
+      row_off(e1, off1);
+      row_off(e2, off2);
+      row_off(e3, off3);
+      row_off(e4, off4);
+      note_valid(0, e0);
+      note_valid(1, e1);
+      note_valid(2, e2);
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) load_k(0, off0, j);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) load_v(0, off0, j);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) load_k(1, off1, j);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) load_v(1, off1, j);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) load_k(2, off2, j);
     publish_barrier<4 * NI>();  // K(t0) has landed
+    if (!active) {
+      int t = t_begin;
+      for (; t + 2 < t_end; t += 2) {
+        pair_top(t);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) load_k((t - t_begin + 3) % NBUF, off3, j);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) load_v((t - t_begin + 2) % NBUF, off2, j);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) load_k((t - t_begin) % NBUF, off4, j);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) load_v((t - t_begin + 3) % NBUF, off3, j);
+        next_offsets(t + 1);
+      }
+      pair_top(t);  // (its loads are past the part's end)
+    } else {
     qk(0, sA);
     if (t_begin >= t_plain) apply_mask(t_begin, 0, sA);
     if (!mem_part && parts_mem > 0 && t_begin * KB < mem_len) {
@@ -805,39 +843,38 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
     l_pend = half_p(sA[0], p0);
 
     int t = t_begin;
-    // next tile unmasked
+    // pairs whose next tiles are plain, then the rest masked
     for (; t + 2 < t_plain; t += 2) {
-      iteration(t, sA, sB, std::false_type{});
-      iteration(t + 1, sB, sA, std::false_type{});
+      pair_top(t);
+      tile_step(t, sA, sB, std::true_type{}, std::false_type{});
+      tile_step(t + 1, sB, sA, std::false_type{}, std::false_type{});
     }
-    if (t + 1 < t_plain) {
-      iteration(t, sA, sB, std::false_type{});
-      copy_state(sA, sB);
-      ++t;
-    }
-    // next tile masked
     for (; t + 2 < t_end; t += 2) {
-      iteration(t, sA, sB, std::true_type{});
-      iteration(t + 1, sB, sA, std::true_type{});
+      pair_top(t);
+      tile_step(t, sA, sB, std::true_type{}, std::true_type{});
+      tile_step(t + 1, sB, sA, std::false_type{}, std::true_type{});
     }
+    pair_top(t);
     if (t + 1 < t_end) {
-      iteration(t, sA, sB, std::true_type{});
+      tile_step(t, sA, sB, std::true_type{}, std::true_type{});
       copy_state(sA, sB);
       ++t;
     }
-    // drain: P and PV of the last tile (then no load is left in flight)
-    publish_barrier<0>();
+    // drain: P and PV of the last tile
     u32x4 w1[2];
-    float psum1 = half_p(sA[1], w1);
-    if (__ballot(psum1 > lazy_bound())) {
+    float l_tile = l_pend + half_p(sA[1], w1);
+    if (__ballot(l_tile > lazy_bound)) {
       force_max(tile_max(sA));
-      l_pend = half_p(sA[0], p0);
-      psum1 = half_p(sA[1], w1);
+      l_tile = half_p(sA[0], p0);
+      l_tile += half_p(sA[1], w1);
     }
-    l_run += l_pend + psum1;
-    if constexpr (MASS) mass_tile(t, l_pend + psum1);
+    l_run += l_tile;
+    if constexpr (MASS) mass_tile(t, l_tile);
     const bf16x8 pb[2][2] = {{as_bf16x8(p0[0]), as_bf16x8(p0[1])}, {as_bf16x8(w1[0]), as_bf16x8(w1[1])}};
     pv((t - t_begin) % NBUF, pb);
+    }
+    publish_barrier<0>();  // no load is left in flight
+    __builtin_amdgcn_s_setprio(0);
   }
 
   // Epilogue: combine the two lane halves' partial sums; write O (bf16, one part)

@@ -1,0 +1,28 @@
+"""The matrix-core attention where its tile loop can go wrong (GPU): key groups of one key (l_I or l_bs
+not a multiple of 8) over more tiles than the position table holds, odd and even tile counts down to one,
+row tiles whose last waves have no rows, and lookup entries to skip in each.  Expected values: the oracle,
+at the bars of the other attention cases."""
+import pytest
+
+from tests.test_gpu_kernels import _attend_case
+
+pytestmark = pytest.mark.gpu
+
+#         dtype, G, Hkv, D, lI, lL, lbs, k_m, past, n_q, B
+CASES = [
+    # single-key groups, 84 and more tiles in one part: the position table moves along
+    ("bf16", 3, 1, 128, 5, 300, 20, 250, 7000, 11, 1),    # 33 rows: one whole wave and one row
+    ("bf16", 4, 1, 64, 8, 300, 36, 160, 9000, 65, 1),     # 260 rows: a row tile of four rows
+    # 8-key groups, l_I and l_bs multiples of 8 but not of a tile
+    ("bf16", 2, 2, 128, 24, 500, 40, 30, 6000, 47, 1),
+    # one, two and three tiles in all
+    ("bf16", 4, 2, 128, 0, 16, 16, 2, 9, 40, 1),
+    ("bf16", 1, 2, 64, 4, 64, 16, 2, 70, 40, 2),
+    ("bf16", 4, 2, 128, 16, 64, 16, 4, 110, 77, 1),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[str(c) for c in CASES])
+@pytest.mark.parametrize("mode", ["parts", "one-part", "skipped-entry", "skipped-entry-one-part"])
+def test_chunk_attend_tiles(case, mode):
+    _attend_case(case, workspace="one-part" not in mode, invalid_entry=mode.startswith("skipped"))
