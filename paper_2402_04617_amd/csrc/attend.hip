@@ -162,15 +162,28 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
   if (decode_eligible(bf16, n_q, G, n_sel)) return min(attend_decode_parts(batch * n_kv_heads, n_virtual), max(1, max_parts));
   const int rows_per_wg = bf16 ? kMfmaRowsPerWg : 16;
   const int key_tile = bf16 ? 64 : 32;
-  const int cap = bf16 ? 8 : 16;
-  const int target = bf16 ? kMfmaTargetWgs : 512;
   const int row_tiles = batch * n_kv_heads * ((G * n_q + rows_per_wg - 1) / rows_per_wg);
   const int n_tiles = (n_virtual + key_tile - 1) / key_tile;
-  int p = (target + row_tiles - 1) / row_tiles;
-  p = min(p, cap);
-  p = min(p, max(1, n_tiles / 2));
-  p = min(p, max(1, max_parts));
-  return max(1, p);
+  const int cap = min(bf16 ? 8 : 16, min(max(1, n_tiles / 2), max(1, max_parts)));
+  if (!bf16) return max(1, min(cap, (512 + row_tiles - 1) / row_tiles));
+  // Matrix-core kernel: one workgroup per compute unit at a time, so a part count
+  // that starts a new round of workgroups for a few of them is worse than a lower
+  // one.  A round costs its longest part plus kPartCost tiles (prologue and
+  // epilogue), and any split the merge, kMergeCost tiles.  (56 row tiles of 108 key
+  // tiles, a 389-query chunk: 5 parts, 280 workgroups, 84.5 us per step; 4 parts,
+  // 224 workgroups, 63.8 us.  A 300-token prompt: 2 parts 25.4 us, 1 part and no
+  // merge 22.9 us.)
+  constexpr int kPartCost = 5, kMergeCost = 3;
+  int best = 1, best_cost = 0;
+  for (int p = 1; p <= cap; ++p) {
+    const int rounds = (row_tiles * p + kMfmaTargetWgs - 1) / kMfmaTargetWgs;
+    const int cost = rounds * (4 * kPartCost + (4 * n_tiles + p - 1) / p) + (p > 1 ? 4 * kMergeCost : 0);
+    if (p == 1 || cost < best_cost) {
+      best = p;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 int attend_max_parts(bool bf16, int G, int n_q, int64_t max_virtual) {

@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   static_assert(tk::kThreads == 64 * NWAVE && 2 * tk::kThreads >= kFusedSelectShort &&
                     tk::kMaxPer * tk::kThreads >= kFusedSelectMax,
                 "select layout");
-  const bool sel_writer = SEL > 0 && rt == 0 && part == 0;
+  const bool sel_writer = SEL > 0 && rt == 0 && part == 0;  // (also without units: the row is then all -1)
   bool sel_here = sel_writer;
   if constexpr (SEL) {
     const int u_t0 = geo.n_init / KB, u_t1 = (geo.n_init + geo.n_sel * geo.block_size + KB - 1) / KB;
@@ -969,8 +969,8 @@ hipError_t launch_attend_mfma(const AttendArgs& a, hipStream_t s) {
   const int n_row_tiles = (R + ROWS_WG - 1) / ROWS_WG;
   const int blocks = n_row_tiles * a.parts * a.batch * a.n_kv_heads;
   const dim3 grid(blocks), block(64 * NWAVE);
-  const bool sel = a.sel_scores != nullptr, mass = sel && a.mass_part != nullptr;
-  if (sel && (a.sel_units < 1 || a.sel_units > kFusedSelectMax)) return hipErrorInvalidValue;
+  const bool sel = a.idx_out != nullptr, mass = sel && a.mass_part != nullptr;
+  if (sel && (a.sel_units < 0 || a.sel_units > kFusedSelectMax)) return hipErrorInvalidValue;
   const bool long_rows = sel && a.sel_units > kFusedSelectShort;
 #define INFLLM_ATTEND_MFMA(DD)                                                                         \
   do {                                                                                                 \

@@ -167,12 +167,12 @@ struct AttendArgs {
   VarLen var;
   int n_local;
   const int32_t* idx;
-  // Lookup inside the attention (sel_scores non-null; matrix-core kernel,
+  // Lookup inside the attention (idx_out non-null; matrix-core kernel,
   // n_units <= kFusedSelectMax, n_sel <= kFusedSelectMaxK): a workgroup whose tiles hold unit
   // keys selects its kv head's n_sel units from the score row itself, with the
   // select of infllm_select_topk, instead of reading idx; the workgroup of row
   // tile 0 and part 0 also writes the row to idx_out (the -1 padding included).
-  const float* sel_scores;  // [batch * n_kv_heads][sel_stride]
+  const float* sel_scores;  // [batch * n_kv_heads][sel_stride]; not read for a sequence that looks up every unit or none
   int64_t sel_stride;
   int sel_units;            // most units in any score row (picks the select's keys per thread)
   int32_t* idx_out;         // [batch * n_kv_heads][geom.idx_stride]
