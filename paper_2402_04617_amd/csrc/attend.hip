@@ -1,9 +1,8 @@
 // Attention dispatch (bfloat16 chunks: matrix-core kernel; bfloat16 decoding:
 // the bandwidth kernel of attend_decode.hip), plus the float32 kernel:
-//  - attend_f32_kernel: float32 inputs (any n_q), vector ALU, exact-exp online
+//  - attend_f32_kernel: float32 inputs (any n_q), float32 matrix cores, expf online
 //    softmax; the float32 accuracy path.  It reads keys through the same
-//    virtual key axis as the other kernels; with the positional remap it holds
-//    both forms of the query and picks one per key (memory or local).
+//    virtual key axis as the other kernels.
 #include "launch.h"
 
 namespace infllm {
@@ -13,23 +12,57 @@ hipError_t launch_attend_decode(const AttendArgs& a, hipStream_t s);
 
 namespace {
 
-__device__ __forceinline__ bool key_visible(const StepGeom& geo, int v, int qi) {
-  const int v_x0 = geo.n_virtual - geo.n_q;
-  return v < geo.n_virtual && (v < v_x0 || v - v_x0 <= qi);
-}
-
 // ---------------------------------------------------------------- float32 path
-template <int D>
-__global__ void __launch_bounds__(256) attend_f32_kernel(AttendArgs a) {
-  constexpr int RW = 16, TPR = 16, DPT = D / TPR, KT = 32;
-  __shared__ __attribute__((aligned(16))) float ks[KT][D];
-  __shared__ __attribute__((aligned(16))) float vs[KT][D];
-  __shared__ int kval[KT];
+// Direct global->LDS load of 16 bytes per lane (lane i lands at lds + 16*i), waited
+// for by the kernel itself.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void lds_load_lane(uint32_t lds, const void* p) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(p) : "m0", "memory");
+}
+#pragma clang diagnostic pop
+#define INFLLM_LDS __attribute__((address_space(3)))
+
+constexpr int kF32Keys = 32;  // keys per tile
+constexpr int kF32Sel = 2048;  // lookup entries kept in LDS
+
+// Float32 attention on the matrix cores (v_mfma_f32_32x32x2_f32: float32 products
+// and sums).  NW waves of 32 query rows each; the workgroup's keys come in tiles of
+// 32 through two LDS buffers, loaded directly one tile ahead.
+//  S^T = K Q^T: A = K rows from LDS, B = the wave's Q rows in registers.  The
+//    contraction may take the dims in any order: a lane's half of k-steps 4i..4i+3
+//    is dims 8i + 4*gsel .. +4, so that one 16-byte read feeds four k-steps.  Even
+//    and odd k-steps go to two accumulators (a shorter chain, and a smaller error).
+//  O^T += V^T P^T: B = the probabilities as S^T leaves them (k-step (a, b) pairs
+//    keys 8a + b and 8a + 4 + b, one per lane half), A = V rows from LDS; output
+//    block db holds dims DBLK*m + db, so that one read feeds all DBLK blocks.
+// Rows of an LDS tile are XOR-swizzled by granule, which makes both reads
+// conflict-free.  What bounds it: the matrix cores' float32 rate (64 cycles per
+// instruction); with one wave per SIMD the softmax (expf, 16 scores per lane and
+// tile) is exposed.  With one vector-ALU dot product and a shuffle reduction per
+// (row, key) instead, a step of 256 queries of 8 heads (D 64) over 2,400 keys took
+// 228 us against 41 now, with an error against 64 bits of 5.7e-7 against 5.2e-7.
+// With the positional remap (ROPE) a wave holds both forms of its query rows; a tile
+// of memory keys takes the one at distance l_L, a tile of local keys the other, and
+// the tile that holds both kinds takes both and picks per key.
+template <int D, int NW, bool ROPE>
+__global__ void __launch_bounds__(64 * NW, 1) attend_f32_kernel(AttendArgs a) {
+  constexpr int KT = kF32Keys, RW = 32 * NW;
+  constexpr int QL = D / 2;             // query dims per lane
+  constexpr int DBLK = D / 32;          // 32-wide output blocks
+  constexpr int GPR = D / 4;            // 16-byte granules per row
+  constexpr int RPI = 64 / GPR;         // rows per load instruction
+  constexpr int NI = KT / (RPI * NW);   // load instructions per wave and tile (K or V)
+  __shared__ __attribute__((aligned(256))) float ks[2][KT * D];
+  __shared__ __attribute__((aligned(256))) float vs[2][KT * D];
+  __shared__ int64_t spos[3][KT];  // store positions of a tile's keys (0 where there is none)
+  __shared__ __attribute__((aligned(4))) uint8_t sval[3][KT];
+  __shared__ int32_t sidx[kF32Sel];
 
   const int G = a.n_q_heads / a.n_kv_heads;
   const int R = G * a.geom.n_q;
   const int n_row_tiles = (R + RW - 1) / RW;
-  const int L = xcd_logical_block(blockIdx.x, gridDim.x);
+  const int L = (int)gridDim.x - 1 - xcd_logical_block(blockIdx.x, gridDim.x);
   const int rt = L % n_row_tiles;
   const int tmp = L / n_row_tiles;
   const int part = tmp % a.parts;
@@ -38,44 +71,43 @@ __global__ void __launch_bounds__(256) attend_f32_kernel(AttendArgs a) {
   // this sequence's step (its own past length in a variable-length batch)
   const SeqStep sq = seq_step(a, b);
   const StepGeom& geo = sq.geom;
-  const int mem_len = sq.mem_len, parts_mem = sq.parts_mem;
+  const int mem_len = sq.mem_len;
 
-  const int n_tiles = (geo.n_virtual + KT - 1) / KT;
-  const int per_part = (n_tiles + a.parts - 1) / a.parts;
-  const int t_begin = part * per_part;
-  int t_end = min(n_tiles, t_begin + per_part);
-  {
-    const int i_max = (min(R, (rt + 1) * RW) - 1) / G;
-    t_end = min(t_end, (geo.n_virtual - geo.n_q + i_max) / KT + 1);
-  }
+  // the tiles the row tile's queries see, split evenly over the parts
+  const int v_x0 = geo.n_virtual - geo.n_q;
+  const int n_tiles = (v_x0 + (min(R, (rt + 1) * RW) - 1) / G) / KT + 1;
+  const int t_begin = (int)((int64_t)n_tiles * part / a.parts), t_end = (int)((int64_t)n_tiles * (part + 1) / a.parts);
 
-  const int tid = threadIdx.x;
-  const int rl = tid / TPR, sub = tid % TPR;
-  const int row = rt * RW + rl;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, gsel = lane >> 5;
+  const int row = rt * RW + wave * 32 + n;
   const bool row_ok = row < R;
+  const bool active = rt * RW + wave * 32 < R;  // whether the wave has rows at all
   const int qi = row_ok ? row / G : 0;
   const int qh = g * G + (row_ok ? row - qi * G : 0);
+  const int vlim = v_x0 + qi;  // last visible key
   const int32_t* idx_row = a.idx + (int64_t)bg * geo.idx_stride;
   const float* kbase = (const float*)a.k_store + (int64_t)bg * a.capacity * D;
   const float* vbase = (const float*)a.v_store + (int64_t)bg * a.capacity * D;
+  const float* krot = ROPE ? (const float*)a.k_rot + (int64_t)bg * a.capacity * D : nullptr;
 
-  // Query pieces: qv as given; with the positional remap qv is the query at its
-  // own position (for L and X) and qm the query turned by R(l_L) (for I and the
-  // units, whose keys are read unrotated).
-  float qv[DPT], qm[DPT], o[DPT];
+  for (int u = tid; u < min(geo.n_sel, kF32Sel); u += 64 * NW) sidx[u] = idx_row[u];
+
+  // Query pieces: qv as given; under the remap qv is the query at its own position
+  // (L and X) and qm the query turned by R(l_L) (I and the units, keys unrotated).
+  float qv[QL], qm[ROPE ? QL : 1];
   const float* qp = (const float*)a.q + (int64_t)(b * a.n_q_heads + qh) * a.q_head_stride + (int64_t)qi * D;
 #pragma unroll
-  for (int e = 0; e < DPT; ++e) {
-    qv[e] = row_ok ? qp[sub * DPT + e] : 0.f;
-    qm[e] = qv[e];
-    o[e] = 0.f;
-  }
-  const bool remap = a.rope.on != 0;
-  const float* krot = (const float*)a.k_rot + (int64_t)bg * a.capacity * D;
-  if (remap) {
+  for (int i = 0; i < QL / 4; ++i) {
+    const f32x4 x = row_ok ? *(const f32x4*)(qp + 8 * i + 4 * gsel) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < DPT / 2; ++j) {
-      const int pr = sub * DPT / 2 + j;
+    for (int e = 0; e < 4; ++e) qv[4 * i + e] = x[e];
+  }
+  if constexpr (ROPE) {
+#pragma unroll
+    for (int j = 0; j < QL / 2; ++j) {
+      const int pr = 4 * (j >> 1) + 2 * gsel + (j & 1);  // the pair held in qv[2j], qv[2j+1]
       const float x0 = qv[2 * j], x1 = qv[2 * j + 1];
       float c, sn;
       rope_cos_sin(a.rope, geo.past_len + qi, pr, c, sn);
@@ -85,61 +117,181 @@ __global__ void __launch_bounds__(256) attend_f32_kernel(AttendArgs a) {
       qm[2 * j + 1] = x0 * a.rope.mem_sin[pr] + x1 * a.rope.mem_cos[pr];
     }
   }
+
+  // positions of tile t's keys, by the first 32 threads
+  auto find_keys = [&](int t) {
+    if (tid >= KT) return;
+    const int v = t * KT + tid;
+    int64_t pos = -1;
+    if (v < geo.n_virtual) {
+      const int w = v - geo.n_init, sel_len = geo.n_sel * geo.block_size;
+      if (v < geo.n_init) {
+        pos = v;
+      } else if (w >= sel_len) {
+        pos = geo.local_begin + (w - sel_len);
+      } else {
+        const int u = w / geo.block_size;
+        const int bu = u < kF32Sel ? sidx[u] : idx_row[u];
+        if (bu >= 0 && bu < geo.n_units) pos = (int64_t)geo.unit_base + (int64_t)bu * geo.block_size + (w - u * geo.block_size);
+      }
+    }
+    const int slot = (t - t_begin) % 3;
+    spos[slot][tid] = pos >= 0 ? pos : 0;  // position 0 is always written; masked
+    sval[slot][tid] = pos >= 0;
+  };
+  const uint32_t lds_k = (uint32_t)(uintptr_t)(INFLLM_LDS float*)ks[0] + NI * wave * 1024;
+  const uint32_t lds_v = (uint32_t)(uintptr_t)(INFLLM_LDS float*)vs[0] + NI * wave * 1024;
+  constexpr uint32_t kTileBytes = KT * D * 4;
+  // Loads of tile t: granule slot c of tile row r holds the row's granule c ^ (r & 15).
+  auto load_tile = [&](int t) {
+    const int slot = (t - t_begin) % 3;
+    const uint32_t buf = ((t - t_begin) & 1) * kTileBytes;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int r = (NI * wave + j) * RPI + lane / GPR;
+      const int gran = (lane % GPR) ^ (r & 15);
+      const int64_t off = spos[slot][r] * D + 4 * gran;
+      const float* kp = ROPE && t * KT + r >= mem_len ? krot : kbase;
+      lds_load_lane(lds_k + buf + j * 1024, kp + off);
+      lds_load_lane(lds_v + buf + j * 1024, vbase + off);
+    }
+  };
+
+  f32x16 o[DBLK];
+#pragma unroll
+  for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
   float m = -__builtin_inff(), l = 0.f;
 
+  // S^T of the tile in buffer `kt` against one form of the query rows
+  auto scores = [&](const float* kt, const float* qx) {
+    f32x16 s0 = {}, s1 = {};
+#pragma unroll
+    for (int i = 0; i < QL / 4; ++i) {
+      const f32x4 kf = *(const f32x4*)(kt + n * D + 4 * ((2 * i + gsel) ^ (n & 15)));
+      s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[0], qx[4 * i], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[1], qx[4 * i + 1], s1, 0, 0, 0);
+      s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[2], qx[4 * i + 2], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[3], qx[4 * i + 3], s1, 0, 0, 0);
+    }
+    return s0 + s1;
+  };
+
+  if (t_begin < t_end) {
+    __syncthreads();  // sidx
+    find_keys(t_begin);
+    find_keys(t_begin + 1);
+    __syncthreads();
+    load_tile(t_begin);
+  }
   for (int t = t_begin; t < t_end; ++t) {
-    for (int e = tid; e < KT * D / 4; e += 256) {
-      const int j = e / (D / 4), c = e - j * (D / 4);
-      const int v = t * KT + j;
-      const int64_t pos = v < geo.n_virtual ? virtual_pos(geo, idx_row, v) : -1;
-      float4 kk = make_float4(0.f, 0.f, 0.f, 0.f), vv = kk;
-      if (pos >= 0) {
-        kk = *(const float4*)((remap && v >= mem_len ? krot : kbase) + pos * D + 4 * c);
-        vv = *(const float4*)(vbase + pos * D + 4 * c);
+    asm volatile("s_waitcnt vmcnt(0)");  // this wave's part of tile t has landed
+    __syncthreads();                     // every wave's has; the other buffer is free
+    if (t + 1 < t_end) load_tile(t + 1);
+    find_keys(t + 2);
+    if (!active) continue;
+    const int buf = (t - t_begin) & 1, slot = (t - t_begin) % 3;
+    f32x16 s;
+    if constexpr (ROPE) {
+      if (t * KT >= mem_len) {
+        s = scores(ks[buf], qv);
+      } else if ((t + 1) * KT <= mem_len) {
+        s = scores(ks[buf], qm);
+      } else {
+        const f32x16 sl = scores(ks[buf], qv);
+        s = scores(ks[buf], qm);
+        const int first_local = mem_len - t * KT - 4 * gsel;
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          if (8 * (j >> 2) + (j & 3) >= first_local) s[j] = sl[j];
       }
-      *(float4*)&ks[j][4 * c] = kk;
-      *(float4*)&vs[j][4 * c] = vv;
-      if (c == 0) kval[j] = pos >= 0;
+    } else {
+      s = scores(ks[buf], qv);
     }
-    __syncthreads();
-    for (int j = 0; j < KT; ++j) {
-      const bool mem_key = remap && t * KT + j < mem_len;  // uniform over the workgroup
-      float part_dot = 0.f;
+    // mask and the tile's maximum (both lane halves of a row)
+    const int lim = vlim - t * KT - 4 * gsel;
+    float mx = -__builtin_inff();
 #pragma unroll
-      for (int e = 0; e < DPT; ++e) part_dot += (mem_key ? qm[e] : qv[e]) * ks[j][sub * DPT + e];
+    for (int j4 = 0; j4 < 4; ++j4) {
+      const uint32_t kv = *(const uint32_t*)&sval[slot][8 * j4 + 4 * gsel];
 #pragma unroll
-      for (int off = TPR / 2; off > 0; off >>= 1) part_dot += __shfl_xor(part_dot, off);
-      const bool vis = kval[j] && key_visible(geo, t * KT + j, qi);
-      if (vis) {
-        const float s = part_dot * a.sm_scale;
-        const float m_new = fmaxf(m, s);
-        const float corr = expf(m - m_new);
-        const float p = expf(s - m_new);
-        l = l * corr + p;
-#pragma unroll
-        for (int e = 0; e < DPT; ++e) o[e] = o[e] * corr + p * vs[j][sub * DPT + e];
-        m = m_new;
+      for (int e = 0; e < 4; ++e) {
+        const int j = 4 * j4 + e;
+        const bool vis = 8 * j4 + e <= lim && ((kv >> (8 * e)) & 0xFFu) != 0;
+        s[j] = vis ? s[j] * a.sm_scale : -__builtin_inff();
+        mx = fmaxf(mx, s[j]);
       }
     }
-    __syncthreads();
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    if (__ballot(mx > m)) {  // some row's maximum grows (the first visible tile included)
+      const float m_new = fmaxf(m, mx);
+      const float corr = m_new == -__builtin_inff() ? 1.f : expf(m - m_new);
+      m = m_new;
+      l *= corr;
+#pragma unroll
+      for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o[db][j] *= corr;
+    }
+    const float base = m == -__builtin_inff() ? 0.f : m;
+    float ls[2] = {0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      s[j] = expf(s[j] - base);
+      ls[j & 1] += s[j];
+    }
+    l += ls[0] + ls[1];
+    typedef float vfrag_t __attribute__((ext_vector_type(DBLK)));
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int r = 8 * (j >> 2) + 4 * gsel + (j & 3);
+      const int d0 = DBLK * n;  // this lane's dims of the row
+      const vfrag_t vf = *(const vfrag_t*)(vs[buf] + r * D + 4 * ((d0 >> 2) ^ (r & 15)) + (d0 & 3));
+#pragma unroll
+      for (int db = 0; db < DBLK; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db], s[j], o[db], 0, 0, 0);
+    }
   }
 
+  const auto lw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+  const float l_tot = __uint_as_float(lw[0]) + __uint_as_float(lw[1]);
   if (!row_ok) return;
-  const float inv = l > 0.f ? 1.f / l : 0.f;
-  const float lse_v = l > 0.f ? m + logf(l) : -__builtin_inff();
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  const float lse_v = l_tot > 0.f ? m + logf(l_tot) : -__builtin_inff();
   const int64_t grow = (int64_t)(b * a.n_q_heads + qh) * geo.n_q + qi;
-  if (a.parts == 1) {
-    float* op = (float*)a.out + (int64_t)(b * a.n_q_heads + qh) * a.out_head_stride + (int64_t)qi * D;
+  const int64_t rows_total = (int64_t)a.batch * a.n_q_heads * geo.n_q;
+  float* op = a.parts == 1 ? (float*)a.out + (int64_t)(b * a.n_q_heads + qh) * a.out_head_stride + (int64_t)qi * D
+                           : (float*)a.part_o + ((int64_t)part * rows_total + grow) * D;
+  typedef float orow_t __attribute__((ext_vector_type(DBLK)));
 #pragma unroll
-    for (int e = 0; e < DPT; ++e) op[sub * DPT + e] = o[e] * inv;
-    if (a.lse != nullptr && sub == 0) a.lse[grow] = lse_v;
-  } else {
-    const int64_t rows_total = (int64_t)a.batch * a.n_q_heads * geo.n_q;
-    float* op = (float*)a.part_o + ((int64_t)part * rows_total + grow) * D;
+  for (int j = 0; j < 16; ++j) {
+    orow_t w;
 #pragma unroll
-    for (int e = 0; e < DPT; ++e) op[sub * DPT + e] = o[e] * inv;
-    if (sub == 0) a.part_lse[(int64_t)part * rows_total + grow] = lse_v;
+    for (int db = 0; db < DBLK; ++db) w[db] = o[db][j] * inv;
+    *(orow_t*)(op + DBLK * (8 * (j >> 2) + 4 * gsel + (j & 3))) = w;
   }
+  if (gsel == 0) {
+    if (a.parts > 1) a.part_lse[(int64_t)part * rows_total + grow] = lse_v;
+    else if (a.lse != nullptr) a.lse[grow] = lse_v;
+  }
+}
+
+// Waves (of 32 rows) per workgroup of the float32 kernel.
+int f32_waves(int R) { return R > 64 ? 4 : R > 32 ? 2 : 1; }
+
+template <int D, int NW>
+void launch_f32(const AttendArgs& a, int blocks, hipStream_t s) {
+  if (a.rope.on) hipLaunchKernelGGL((attend_f32_kernel<D, NW, true>), dim3(blocks), dim3(64 * NW), 0, s, a);
+  else hipLaunchKernelGGL((attend_f32_kernel<D, NW, false>), dim3(blocks), dim3(64 * NW), 0, s, a);
+}
+template <int D>
+void launch_f32_d(const AttendArgs& a, hipStream_t s) {
+  const int R = a.n_q_heads / a.n_kv_heads * a.geom.n_q, nw = f32_waves(R);
+  const int blocks = ((R + 32 * nw - 1) / (32 * nw)) * a.parts * a.batch * a.n_kv_heads;
+  if (nw == 4) launch_f32<D, 4>(a, blocks, s);
+  else if (nw == 2) launch_f32<D, 2>(a, blocks, s);
+  else launch_f32<D, 1>(a, blocks, s);
 }
 
 bool decode_eligible(bool bf16, int n_q, int G, int n_sel) {
@@ -160,23 +312,24 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
                         int max_parts) {
   const int G = n_q_heads / n_kv_heads;
   if (decode_eligible(bf16, n_q, G, n_sel)) return min(attend_decode_parts(batch * n_kv_heads, n_virtual), max(1, max_parts));
-  const int rows_per_wg = bf16 ? kMfmaRowsPerWg : 16;
-  const int key_tile = bf16 ? 64 : 32;
-  const int row_tiles = batch * n_kv_heads * ((G * n_q + rows_per_wg - 1) / rows_per_wg);
+  const int R = G * n_q;
+  const int rows_per_wg = bf16 ? kMfmaRowsPerWg : 32 * f32_waves(R);
+  const int key_tile = bf16 ? 64 : kF32Keys;
+  const int row_tiles = batch * n_kv_heads * ((R + rows_per_wg - 1) / rows_per_wg);
   const int n_tiles = (n_virtual + key_tile - 1) / key_tile;
   const int cap = min(bf16 ? 8 : 16, min(max(1, n_tiles / 2), max(1, max_parts)));
-  if (!bf16) return max(1, min(cap, (512 + row_tiles - 1) / row_tiles));
-  // Matrix-core kernel: one workgroup per compute unit at a time, so a part count
-  // that starts a new round of workgroups for a few of them is worse than a lower
-  // one.  A round costs its longest part plus kPartCost tiles (prologue and
-  // epilogue), and any split the merge, kMergeCost tiles.  (56 row tiles of 108 key
-  // tiles, a 389-query chunk: 5 parts, 280 workgroups, 84.5 us per step; 4 parts,
-  // 224 workgroups, 63.8 us.  A 300-token prompt: 2 parts 25.4 us, 1 part and no
-  // merge 22.9 us.)
+  // Both kernels put one wave on a SIMD's matrix core (float32) or eight on a compute
+  // unit's (bf16) at a time, so a part count that starts a new round of workgroups for a few of
+  // them is worse than a lower one.  A round costs its longest part plus kPartCost
+  // tiles (prologue and epilogue), and any split the merge, kMergeCost tiles.  (56 row
+  // tiles of 108 key tiles, a 389-query chunk: 5 parts, 280 workgroups, 84.5 us per
+  // step; 4 parts, 224 workgroups, 63.8 us.  A 300-token prompt: 2 parts 25.4 us, 1
+  // part and no merge 22.9 us.)
   constexpr int kPartCost = 5, kMergeCost = 3;
+  const int per_round = bf16 ? kMfmaTargetWgs : kMfmaTargetWgs * 4 / f32_waves(R);
   int best = 1, best_cost = 0;
   for (int p = 1; p <= cap; ++p) {
-    const int rounds = (row_tiles * p + kMfmaTargetWgs - 1) / kMfmaTargetWgs;
+    const int rounds = (row_tiles * p + per_round - 1) / per_round;
     const int cost = rounds * (4 * kPartCost + (4 * n_tiles + p - 1) / p) + (p > 1 ? 4 * kMergeCost : 0);
     if (p == 1 || cost < best_cost) {
       best = p;
@@ -201,12 +354,8 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t s) {
   const int G = a.n_q_heads / a.n_kv_heads;
   if (decode_eligible(a.bf16, a.geom.n_q, G, a.geom.n_sel)) return launch_attend_decode(a, s);
   if (a.bf16) return launch_attend_mfma(a, s);
-  const int R = G * a.geom.n_q;
-  const int blocks = ((R + 15) / 16) * a.parts * a.batch * a.n_kv_heads;
-  if (a.head_dim == 128)
-    hipLaunchKernelGGL(attend_f32_kernel<128>, dim3(blocks), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(attend_f32_kernel<64>, dim3(blocks), dim3(256), 0, s, a);
+  if (a.head_dim == 128) launch_f32_d<128>(a, s);
+  else launch_f32_d<64>(a, s);
   return hipGetLastError();
 }
 

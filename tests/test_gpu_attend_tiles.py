@@ -26,3 +26,21 @@ CASES = [
 @pytest.mark.parametrize("mode", ["parts", "one-part", "skipped-entry", "skipped-entry-one-part"])
 def test_chunk_attend_tiles(case, mode):
     _attend_case(case, workspace="one-part" not in mode, invalid_entry=mode.startswith("skipped"))
+
+
+# The float32 kernel at the edges of its tiles (32 keys, 32 rows a wave, 1, 2 or 4 waves): one row to several
+# row tiles, part and tile remainders, a lookup longer than the entries it keeps in LDS.
+F32_CASES = [
+    ("f32", 1, 2, 128, 5, 40, 12, 6, 300, 1, 1),       # one row
+    ("f32", 3, 1, 64, 16, 100, 20, 5, 700, 11, 2),     # 33 rows: two waves
+    ("f32", 1, 1, 128, 8, 64, 32, 9, 900, 65, 1),      # 65 rows: four waves
+    ("f32", 4, 2, 64, 0, 33, 7, 40, 500, 33, 1),       # 132 rows: a second row tile of four rows
+    ("f32", 2, 1, 128, 16, 64, 16, 4, 20, 31, 1),      # no units yet
+    ("f32", 1, 1, 64, 4, 40, 2, 2100, 5000, 9, 1),     # 2,100 entries
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=[str(c) for c in F32_CASES])
+@pytest.mark.parametrize("mode", ["parts", "one-part", "skipped-entry"])
+def test_chunk_attend_f32_tiles(case, mode):
+    _attend_case(case, workspace=mode != "one-part", invalid_entry=mode == "skipped-entry")
