@@ -93,8 +93,11 @@ bool remap(const infllm_params* p) { return p->rope_inv_freq != nullptr; }
 // Units scored by their mean key: no representative scores, so no query ring.
 bool mean_repr(const infllm_params* p) { return p->repr_mode == INFLLM_REPR_MEAN; }
 
-// Rotary tables of the positional remap, formed in float64 on the host.
-RopeArgs rope_args(const infllm_params* p) {
+// Rotary tables of the positional remap, formed in float64 on the host: the
+// revolutions per position (for keys and queries at their own positions) and the
+// turn by R(l_L) (for queries that meet memory keys), whichever a kernel reads --
+// the sines and cosines cost the host microseconds per call.
+RopeArgs rope_args(const infllm_params* p, bool positions, bool memory) {
   RopeArgs r;
   std::memset(&r, 0, sizeof(r));
   if (!remap(p)) return r;
@@ -102,9 +105,14 @@ RopeArgs rope_args(const infllm_params* p) {
   const double two_pi = 6.283185307179586476925286766559;
   for (int i = 0; i < p->head_dim / 2; ++i) {
     const double th = p->rope_inv_freq[i];
-    r.rev[i] = th / two_pi;
-    r.mem_cos[i] = (float)std::cos((double)p->n_local * th);
-    r.mem_sin[i] = (float)std::sin((double)p->n_local * th);
+    if (positions) {
+      const double turns = th / two_pi, whole = std::floor(turns);
+      r.rev[i] = (uint64_t)((turns - whole) * 0x1p64);  // the difference is exact and below 1
+    }
+    if (memory) {
+      r.mem_cos[i] = (float)std::cos((double)p->n_local * th);
+      r.mem_sin[i] = (float)std::sin((double)p->n_local * th);
+    }
   }
   return r;
 }
@@ -211,8 +219,9 @@ infllm_status prepare_attend(const infllm_params* p, const infllm_memory* m, con
   const int64_t rows = (int64_t)m->batch * p->n_q_heads * n_q;
   const size_t per_part = rows > 0 ? (size_t)rows * part_row_bytes(p) : 1;
   const int max_parts = (workspace == nullptr) ? 0 : (int)(workspace_bytes / per_part > 4096 ? 4096 : workspace_bytes / per_part);
+  int row_waves = 0;
   int parts = attend_choose_parts(bf16, m->batch, p->n_q_heads, p->n_kv_heads, n_q, n_sel, (int)n_virtual,
-                                  max_parts);
+                                  max_parts, &row_waves);
   if (parts < 1) return INFLLM_E_WORKSPACE;
   // With the remap, memory keys (I and the units) and local keys go to
   // different parts, in proportion to their counts.
@@ -252,12 +261,13 @@ infllm_status prepare_attend(const infllm_params* p, const infllm_memory* m, con
   a->k_rot = m->k_rot;
   a->parts_mem = parts_mem;
   a->mem_len = (int)mem_len;
-  a->rope = rope_args(p);
+  a->rope = rope_args(p, true, true);
   a->n_local = p->n_local;
   a->idx = idx;
   a->out = out;
   a->lse = lse;
   a->parts = parts;
+  a->row_waves = row_waves;
   partial_layout(p, workspace, parts, rows, &a->part_o, &a->part_lse, &a->part_exp);
   a->bf16 = bf16;
   return INFLLM_OK;
@@ -337,7 +347,7 @@ infllm_status prep_append(const infllm_params* p, const infllm_memory* m, const 
   a->qprefix = m->qprefix;
   a->rpart = m->rpart;
   a->k_rot = m->k_rot;
-  a->rope = rope_args(p);
+  a->rope = rope_args(p, true, false);
   a->var.on = 0;
   a->mean_repr = mean_repr(p);
   a->bf16 = p->dtype == INFLLM_BF16;
@@ -414,7 +424,7 @@ infllm_status prep_score(const infllm_params* p, const infllm_memory* m, const v
   a->unit_ksum = m->unit_ksum;
   a->scores = scores;
   a->qbar_parts = (float*)workspace;
-  a->rope = rope_args(p);
+  a->rope = rope_args(p, false, true);
   a->bf16 = p->dtype == INFLLM_BF16;
   return INFLLM_OK;
 }
@@ -636,7 +646,7 @@ static infllm_status prep_unit_mass(const infllm_params* p, const infllm_memory*
   a->lse = lse;
   a->mass = mass;
   a->freq = part.n_units > 0 ? freq : nullptr;
-  a->rope = rope_args(p);
+  a->rope = rope_args(p, false, true);
   a->bf16 = p->dtype == INFLLM_BF16;
   return INFLLM_OK;
 }
@@ -850,7 +860,10 @@ infllm_status infllm_step_varlen(const infllm_params* p, const infllm_memory* m,
     new_max = std::max(new_max, bb.n_new);
     parts = std::max(parts, tb.parts);
     n_sel_max = std::max(n_sel_max, tb.geom.n_sel);
-    nv_max = std::max(nv_max, tb.geom.n_virtual);
+    if (tb.geom.n_virtual > nv_max) {
+      nv_max = tb.geom.n_virtual;
+      at.row_waves = tb.row_waves;
+    }
     const int64_t m0 = (int64_t)p->n_init + (int64_t)units_built[b] * p->block_size;
     if (bb.n_new > 0 && !mean && m0 < past + n_q - m->ring) fuse = false;
     ba.var_first[b] = units_built[b];

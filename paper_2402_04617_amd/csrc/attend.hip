@@ -309,13 +309,12 @@ int attend_decode_parts(int bh, int n_virtual) {
 }
 
 int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int n_q, int n_sel, int n_virtual,
-                        int max_parts) {
+                        int max_parts, int* row_waves) {
+  *row_waves = kMfmaWaves;
   const int G = n_q_heads / n_kv_heads;
   if (decode_eligible(bf16, n_q, G, n_sel)) return min(attend_decode_parts(batch * n_kv_heads, n_virtual), max(1, max_parts));
   const int R = G * n_q;
-  const int rows_per_wg = bf16 ? kMfmaRowsPerWg : 32 * f32_waves(R);
   const int key_tile = bf16 ? 64 : kF32Keys;
-  const int row_tiles = batch * n_kv_heads * ((R + rows_per_wg - 1) / rows_per_wg);
   const int n_tiles = (n_virtual + key_tile - 1) / key_tile;
   const int cap = min(bf16 ? 8 : 16, min(max(1, n_tiles / 2), max(1, max_parts)));
   // Both kernels put one wave on a SIMD's matrix core (float32) or eight on a compute
@@ -326,14 +325,24 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
   // step; 4 parts, 224 workgroups, 63.8 us.  A 300-token prompt: 2 parts 25.4 us, 1
   // part and no merge 22.9 us.)
   constexpr int kPartCost = 5, kMergeCost = 3;
-  const int per_round = bf16 ? kMfmaTargetWgs : kMfmaTargetWgs * 4 / f32_waves(R);
   int best = 1, best_cost = 0;
-  for (int p = 1; p <= cap; ++p) {
-    const int rounds = (row_tiles * p + per_round - 1) / per_round;
-    const int cost = rounds * (4 * kPartCost + (4 * n_tiles + p - 1) / p) + (p > 1 ? 4 * kMergeCost : 0);
-    if (p == 1 || cost < best_cost) {
-      best = p;
-      best_cost = cost;
+  // (costs in quarters of a tile of a full workgroup; a half-filled bf16 workgroup,
+  // one wave per SIMD, takes about kHalfTile/4 of that tile's time: a 300-token
+  // prompt as 80 half-filled workgroups 17.7 us per step, as 40 full ones 21)
+  constexpr int kHalfTile = 3;
+  for (int half = 0; half < (bf16 ? 2 : 1); ++half) {
+    const int waves = bf16 ? (half ? kMfmaWaves / 2 : kMfmaWaves) : f32_waves(R);
+    const int row_tiles = batch * n_kv_heads * ((R + 32 * waves - 1) / (32 * waves));
+    const int per_round = bf16 ? kMfmaTargetWgs : kMfmaTargetWgs * 4 / waves;
+    const int tile_cost = half || R <= 32 * kMfmaWaves / 2 ? kHalfTile : 4;
+    for (int p = 1; p <= cap; ++p) {
+      const int rounds = (row_tiles * p + per_round - 1) / per_round;
+      const int cost = rounds * (4 * kPartCost + (tile_cost * n_tiles + p - 1) / p) + (p > 1 ? 4 * kMergeCost : 0);
+      if ((half == 0 && p == 1) || cost < best_cost) {
+        best = p;
+        best_cost = cost;
+        *row_waves = waves;
+      }
     }
   }
   return best;

@@ -26,9 +26,7 @@ namespace infllm {
 namespace {
 
 constexpr int KB = 64;      // keys per tile
-constexpr int NWAVE = 8;
-constexpr int ROWS_WG = 32 * NWAVE;
-static_assert(ROWS_WG == kMfmaRowsPerWg, "row tiling shared with the part chooser");
+constexpr int NWAVE = kMfmaWaves;
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 #define INFLLM_LDS __attribute__((address_space(3)))
@@ -45,6 +43,10 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // Wave-uniform base address plus a per-lane 32-bit byte offset.
 __device__ __forceinline__ void lds_load(uint32_t lds, const void* base, uint32_t off) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "m0");
+}
+// A full per-lane address.
+__device__ __forceinline__ void lds_load_lane(uint32_t lds, const void* p) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(p) : "m0");
 }
 #pragma clang diagnostic pop
 
@@ -75,9 +77,9 @@ template <int D>
 __device__ __forceinline__ int tile_off(int r, int g) { return r * D + 8 * (g ^ swz<D>(r)); }
 
 constexpr int NBUF = 4;         // K and V tile buffers: a pair of tiles in use, the next pair in flight
-constexpr int kMaskCost = 6;  // cost of a masked tile, in quarters of a plain tile (measured ~1.5x)
-constexpr int kSelTiles4 = 5;  // the in-prologue unit selection, in quarters of a plain tile
-constexpr int kSelTiles4Long = 16;  // the same for rows of more than kFusedSelectShort units
+constexpr float kMaskCost = 1.5f;  // cost of a masked tile, in plain tiles
+constexpr float kSelTiles = 1.f;  // the in-prologue unit selection, in plain tiles
+constexpr float kSelTilesLong = 2.f;  // the same for rows of more than kFusedSelectShort units
 constexpr int kRowTable = 4096;  // key-group positions kept in LDS (512 tiles of 8-key groups, 64 of single keys)
 constexpr int kSelLds = 1024;    // lookup entries kept in LDS
 static_assert(kFusedSelectMaxK <= kSelLds, "a selected lookup row fits in LDS");
@@ -91,20 +93,24 @@ struct Smem {
   uint32_t rows[kRowTable];  // store position of each key group of a window of tiles (kNoRow: skipped entry)
   int32_t sidx[kSelLds];    // the lookup row (its first kSelLds entries)
   uint8_t kvalid[NBUF][KB];
+  int sel_ok;
 };
 
 // Publish LDS tiles to the workgroup: wait until at most N of this wave's
 // direct loads are still in flight (older loads -- the tiles about to be read
 // -- have landed in LDS) and its own LDS traffic is done, then barrier.  Written
 // out so that no wait for the younger loads is implied.
-template <int N>
-__device__ __forceinline__ void publish_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N));
+__device__ __forceinline__ void lds_barrier() {
   // LDS-only fences: order this wave's LDS accesses around the barrier without
   // a wait for its outstanding global loads.
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+template <int N>
+__device__ __forceinline__ void publish_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N));
+  lds_barrier();
 }
 
 // SEL > 0: the workgroups select the lookup themselves from a.sel_scores, SEL
@@ -125,18 +131,31 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   static_assert(NI * NWAVE * RPI == KB, "tile rows covered exactly once");
   __shared__ __attribute__((aligned(256))) Smem<D> sm;
 
-  const int G = a.n_q_heads / a.n_kv_heads;
+  // The prologue is latency: 10 us for a selecting workgroup and 6.7 for another of a
+  // 128K step's 79, now 7.4 and 4.7 of 71 (arguments, divisions and the part bounds
+  // 1.8 -> 0.9; selection 4.6 -> 2.9; the queries and K(t0) load while the position
+  // table is filled).
+  // Every argument the prologue reads, requested at once: read where they are used,
+  // their cold cache lines were waited for one after another.
+  asm volatile("" ::"s"(a.batch), "s"(a.capacity), "s"(a.q_head_stride), "s"(a.q), "s"(a.k_store), "s"(a.v_store),
+               "s"(a.parts), "s"(a.row_waves), "s"(a.n_q_heads), "s"(a.n_kv_heads));
+  asm volatile("" ::"s"(a.geom.n_init), "s"(a.geom.n_units), "s"(a.geom.n_sel), "s"(a.geom.block_size),
+               "s"(a.geom.unit_base), "s"(a.geom.idx_stride), "s"(a.geom.local_begin), "s"(a.geom.past_len),
+               "s"(a.geom.n_q), "s"(a.geom.n_virtual));
+  asm volatile("" ::"s"(a.mem_len), "s"(a.parts_mem), "s"(a.rope.on), "s"(a.var.on), "s"(a.d_row_tiles.mul),
+               "s"(a.d_parts.mul), "s"(a.d_kv.mul), "s"(a.d_group.mul), "s"(a.d_block.mul), "s"(a.sel_scores),
+               "s"(a.sel_stride));
+  const int G = (int)a.d_group.d;
   const int R = G * a.geom.n_q;
-  const int n_row_tiles = (R + ROWS_WG - 1) / ROWS_WG;
+  const int n_row_tiles = (int)a.d_row_tiles.d;
+  const int rows_wg = 32 * a.row_waves;
   // XCD-aware order, reversed so that the workgroups dispatched first are those
   // with the most work: the last key part (it holds the causal diagonal of X) and
   // the last row tiles (their queries see the most of X)
   const int L = (int)gridDim.x - 1 - xcd_logical_block(blockIdx.x, gridDim.x);
-  const int rt = L % n_row_tiles;
-  const int tmp = L / n_row_tiles;
-  const int part = tmp % a.parts;
-  const int bg = tmp / a.parts;
-  const int b = bg / a.n_kv_heads, g = bg - b * a.n_kv_heads;
+  const int tmp = div_by(L, a.d_row_tiles), rt = L - tmp * n_row_tiles;
+  const int bg = div_by(tmp, a.d_parts), part = tmp - bg * a.parts;
+  const int b = div_by(bg, a.d_kv), g = bg - b * a.n_kv_heads;
   // this sequence's step (its own past length in a variable-length batch)
   const SeqStep sq = seq_step(a, b);
   const StepGeom& geo = sq.geom;
@@ -162,34 +181,35 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   }
   // The parts split the tiles this row tile's queries see by cost rather than by
   // count, so that they end together: a masked tile (the causal diagonal) costs
-  // kMaskCost/4 plain tiles, and with the selection inside (SEL) the parts that
-  // read unit keys also select the units (see below), kSelTiles4/4 tiles of work
+  // kMaskCost plain tiles, and with the selection inside (SEL) the parts that
+  // read unit keys also select the units (see below), kSelTiles tiles of work
   // each: the tiles up to the end of the units are charged that work spread over
   // them, for the share of the parts expected to fall there.
   const int v_x0 = geo.n_virtual - geo.n_q;  // first current-token key
-  const int qi_min = min(R - 1, rt * ROWS_WG) / G, qi_max = (min(R, (rt + 1) * ROWS_WG) - 1) / G;
+  const int qi_min = div_by(min(R - 1, rt * rows_wg), a.d_group);
+  const int qi_max = div_by(min(R, (rt + 1) * rows_wg) - 1, a.d_group);
   const int vis_end = mem_part ? mem_len : v_x0 + qi_min + 1;  // every row of the tile sees the keys below
   rt1 = min(rt1, (v_x0 + qi_max) / KB + 1);                    // later tiles are fully causal-masked
-  auto part_bound = [&](int pp) -> int {  // first tile of part pp of rparts (costs in 1/64 of a plain tile)
-    const int a_m = min(max(vis_end / KB, rt0), rt1);  // first masked tile
-    constexpr int64_t kPlain = 64, kMask = 16 * kMaskCost;
-    int s_end = rt0;
-    int64_t kSel = kPlain;
-    if constexpr (SEL > 0) {
+  const int a_m = min(max(vis_end / KB, rt0), rt1);            // first masked tile
+  int s_end = rt0;                                             // end of the tiles charged the selection
+  float c_seltile = 1.f;
+  if constexpr (SEL > 0) {
+    if (geo.n_sel > 0 && geo.n_sel < geo.n_units) {
       const int u_end = (geo.n_init + geo.n_sel * geo.block_size + KB - 1) / KB;
-      constexpr int64_t kSel4 = SEL > 2 ? kSelTiles4Long : kSelTiles4;
-      if (geo.n_sel > 0 && geo.n_sel < geo.n_units) {
-        s_end = min(max(u_end, rt0), a_m);
-        kSel += (kPlain * kSel4 * rparts) / (4 * max(1, rt1 - rt0));
-      }
+      s_end = min(max(u_end, rt0), a_m);
+      c_seltile += (SEL > 2 ? kSelTilesLong : kSelTiles) * (float)rparts * __builtin_amdgcn_rcpf((float)max(1, rt1 - rt0));
     }
-    const int64_t c_sel = kSel * (s_end - rt0);
-    const int64_t c_plain = c_sel + kPlain * (a_m - s_end);
-    const int64_t c_all = c_plain + kMask * (rt1 - a_m);
-    const int64_t c = c_all * pp / rparts;
-    if (c <= c_sel) return rt0 + (int)((c + kSel - 1) / kSel);
-    if (c <= c_plain) return s_end + (int)((c - c_sel + kPlain - 1) / kPlain);
-    return a_m + (int)((c - c_plain + kMask - 1) / kMask);
+  }
+  const float c_sel = c_seltile * (float)(s_end - rt0), c_plain = c_sel + (float)(a_m - s_end);
+  const float c_part = (c_plain + kMaskCost * (float)(rt1 - a_m)) * __builtin_amdgcn_rcpf((float)rparts);
+  auto part_bound = [&](int pp) -> int {  // first tile of part pp of rparts (the same in every workgroup)
+    if (pp == 0) return rt0;
+    if (pp == rparts) return rt1;
+    const float c = c_part * (float)pp;
+    const int t = c <= c_sel     ? rt0 + (int)(c * __builtin_amdgcn_rcpf(c_seltile) + 0.5f)
+                  : c <= c_plain ? s_end + (int)(c - c_sel + 0.5f)
+                                 : a_m + (int)((c - c_plain) * (1.f / kMaskCost) + 0.5f);
+    return min(max(t, rt0), rt1);
   };
   const int t_begin = part_bound(rpart);
   const int t_end = part_bound(rpart + 1);
@@ -198,13 +218,15 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, gsel = lane >> 5;
-  const int row = rt * ROWS_WG + wave * 32 + n;
-  const bool row_ok = row < R;
-  // A wave whose 32 rows all lie past the last query (a short or ragged chunk)
-  // computes nothing: it only loads its rows of the tiles and keeps the barriers,
-  // which leaves its SIMD's matrix core and the power budget to the others.
-  const bool active = rt * ROWS_WG + wave * 32 < R;
-  const int qi = row_ok ? row / G : 0;
+  const int row0 = rt * rows_wg + wave * 32;  // the wave's first row
+  // A wave without rows (past the last query of a short or ragged chunk, or of the
+  // unused half of a half-filled workgroup) computes nothing: it only loads its rows
+  // of the tiles and keeps the barriers, which leaves its SIMD's matrix core and the
+  // power budget to the others.
+  const bool active = wave < a.row_waves && row0 < R;
+  const int row = row0 + n;
+  const bool row_ok = active && row < R;
+  const int qi = row_ok ? div_by(row, a.d_group) : 0;
   // last virtual key this row may see: causal within X (which also excludes the
   // ragged end), or for a memory part of the remap the last memory key
   const int vlim = mem_part ? mem_len - 1 : v_x0 + qi;
@@ -214,92 +236,142 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   const bf16_t* kbase = (const bf16_t*)(remap && !mem_part ? a.k_rot : a.k_store) + (int64_t)bg * a.capacity * D;
   const bf16_t* vbase = (const bf16_t*)a.v_store + (int64_t)bg * a.capacity * D;
 
-  // The lookup row goes to LDS (run starts then read LDS, not global memory) in
-  // the same round trip as the Q rows; one barrier publishes it together with
-  // the check for skipped (out-of-range) entries, which send every tile through
-  // the per-key gather path and the validity mask.
-  bool bad = false;
-  if constexpr (!SEL) {
-    for (int u = tid; u < geo.n_sel; u += 64 * NWAVE) {
-      const int x = idx_row[u];
-      if (u < kSelLds) sm.sidx[u] = x;
-      bad |= (x < 0 || x >= geo.n_units);
-    }
-  }
-  // Lookup inside the attention: a workgroup selects the units itself when a
-  // tile it reads (its own, the run-start table's and the loads issued ahead:
-  // [t_begin, t_end + 4)) holds unit keys; the workgroup of row tile 0 and part
-  // 0 always does, and writes the row out.  Every entry is then valid.  The
-  // score row is loaded here, its latency overlapping the Q loads below.
+  // Whether a tile this workgroup loads (its own and those issued ahead, [t_begin,
+  // t_end + 7)) may hold unit keys; only then does it need the lookup.
+  const int u_t0 = geo.n_init / KB, u_t1 = (geo.n_init + geo.n_sel * geo.block_size + KB - 1) / KB;
+  const bool units_here = t_begin < t_end && t_begin < u_t1 && t_end + 7 > u_t0;
+  // Lookup inside the attention: such a workgroup selects the units itself; the
+  // workgroup of row tile 0 and part 0 always does, and writes the row out (also
+  // without units: it is then all -1).  Every entry is valid.
   static_assert(SEL == 0 || SEL == 2 || SEL == tk::kMaxPer, "select keys per thread");
   static_assert(tk::kThreads == 64 * NWAVE && 2 * tk::kThreads >= kFusedSelectShort &&
                     tk::kMaxPer * tk::kThreads >= kFusedSelectMax,
                 "select layout");
-  const bool sel_writer = SEL > 0 && rt == 0 && part == 0;  // (also without units: the row is then all -1)
-  bool sel_here = sel_writer;
-  if constexpr (SEL) {
-    const int u_t0 = geo.n_init / KB, u_t1 = (geo.n_init + geo.n_sel * geo.block_size + KB - 1) / KB;
-    sel_here |= t_begin < u_t1 && t_end + 4 > u_t0;
-  }
+  const bool sel_writer = SEL > 0 && rt == 0 && part == 0;
+  const bool sel_here = SEL > 0 && (sel_writer || units_here);
   const bool sel_all = geo.n_sel == 0 || geo.n_sel == geo.n_units;  // every unit (or none) is looked up
-  constexpr int SK = SEL > 0 ? SEL : 1;
-  uint32_t skey[SK] = {};
-  if (SEL > 0 && sel_here && !sel_all) {
-    const float* srow = a.sel_scores + (int64_t)bg * a.sel_stride;
+  const bool sel_waves = geo.n_sel <= tk::kWaveK;                   // by the single-wave select
+  const float* srow = SEL > 0 ? a.sel_scores + (int64_t)bg * a.sel_stride : nullptr;
+  // scores of the single-wave select: short rows in the first wave, 16 per lane; long
+  // rows 16 per lane of every wave (loaded before the queries, whose latency overlaps)
+  constexpr int WPER = 16;
+  uint32_t wkey[WPER] = {};
+  if (SEL > 0 && sel_here && !sel_all && sel_waves && (SEL > 2 || wave == 0)) {
 #pragma unroll
-    for (int j = 0; j < SK; ++j) skey[j] = tk::order_key(srow[min(tid + j * tk::kThreads, geo.n_units - 1)]);
+    for (int j = 0; j < WPER; ++j)
+      wkey[j] = __float_as_uint(srow[min(wave * 64 * WPER + 64 * j + lane, geo.n_units - 1)]);
   }
-  // Q rows of this wave as the B operand (8 bf16 per lane per k-step).
-  bf16x8 qreg[KSTEPS];
-  {
-    const bf16_t* qp = (const bf16_t*)a.q + (int64_t)(b * a.n_q_heads + qh) * a.q_head_stride + (int64_t)qi * D;
+
+  // The wave's query rows go to LDS first, whole rows at a time, into the V buffers
+  // (256 rows fill the four exactly; V loads start once they are read back), swizzled
+  // like a K tile.  Loading them into registers directly made the compiler wait for
+  // every tile load issued behind them.
+  const uint32_t lds_k0 = (uint32_t)(uintptr_t)(INFLLM_LDS bf16_t*)sm.k[0];
+  const uint32_t lds_v0 = (uint32_t)(uintptr_t)(INFLLM_LDS bf16_t*)sm.v[0];
+  constexpr int NQ = 32 / RPI;  // load instructions for 32 rows
+  const uint32_t lds_q = lds_v0 + wave * 32 * D * 2;
+  // (query, head) of the rows this lane moves, here and in the epilogue: row0 + lane /
+  // CH and every RPI-th after it, stepped without a division
+  const int li0 = div_by(row0 + lane / CH, a.d_group), lh0 = row0 + lane / CH - li0 * G;
+  const int step_i = div_by(RPI, a.d_group), step_h = RPI - step_i * G;
+  auto next_row = [&](int& i, int& h) {
+    i += step_i;
+    h += step_h;
+    const bool wrap = h >= G;
+    h -= wrap ? G : 0;
+    i += wrap ? 1 : 0;
+  };
+  if (active) {
+    // within the kv head's query rows 32-bit byte offsets do, unless the heads lie
+    // very far apart
+    const bf16_t* qg = (const bf16_t*)a.q + (int64_t)(b * a.n_q_heads + g * G) * a.q_head_stride;
+    const bool near = (int64_t)G * a.q_head_stride < (1ll << 30);
+    int i = li0, h = lh0;
 #pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) {
-      u32x4 raw = row_ok ? *(const u32x4*)(qp + 16 * s + 8 * gsel) : u32x4{0, 0, 0, 0};
-      if (remap) {
-        // memory parts: the query turned by R(l_L); local parts: at its own position
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int pr = 8 * s + 4 * gsel + j;  // the pair held in word j
-          float cs, sn;
-          if (mem_part) {
-            cs = a.rope.mem_cos[pr];
-            sn = a.rope.mem_sin[pr];
-          } else {
-            rope_cos_sin(a.rope, geo.past_len + qi, pr, cs, sn);
-          }
-          const float x0 = __uint_as_float(raw[j] << 16), x1 = __uint_as_float(raw[j] & 0xFFFF0000u);
-          raw[j] = (uint32_t)f32_to_bf16(x0 * cs - x1 * sn) | ((uint32_t)f32_to_bf16(x0 * sn + x1 * cs) << 16);
-        }
+    for (int j = 0; j < NQ; ++j) {
+      const int rr = RPI * j + lane / CH;
+      const bool in = row0 + rr < R;
+      const int ii = in ? i : 0, hh = in ? h : 0;
+      const int gran = (lane % CH) ^ swz<D>(rr);
+      if (near) {
+        lds_load(lds_q + j * 1024, qg, 2u * ((uint32_t)hh * (uint32_t)a.q_head_stride + (uint32_t)ii * D + 8u * gran));
+      } else {
+        lds_load_lane(lds_q + j * 1024, qg + hh * a.q_head_stride + (int64_t)ii * D + 8 * gran);
       }
-      qreg[s] = __builtin_bit_cast(bf16x8, raw);
+      next_row(i, h);
     }
   }
-  if (SEL > 0 && sel_here) {
+  // The lane's rotary table entries under the remap (granule lane % CH, four pairs)
+  uint64_t rev[4];
+  float mcos[4], msin[4];
+  if (remap) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      rev[j] = a.rope.rev[4 * (lane % CH) + j];
+      mcos[j] = a.rope.mem_cos[4 * (lane % CH) + j];
+      msin[j] = a.rope.mem_sin[4 * (lane % CH) + j];
+    }
+  }
+
+  bool has_invalid = false;
+  if constexpr (SEL == 0) {
+    // The lookup row goes to LDS; skipped (out-of-range) entries send every tile
+    // through the validity mask.
+    if (units_here) {
+      bool bad = false;
+      for (int u = tid; u < geo.n_sel; u += 64 * NWAVE) {
+        const int x = idx_row[u];
+        if (u < kSelLds) sm.sidx[u] = x;
+        bad |= (x < 0 || x >= geo.n_units);
+      }
+      has_invalid = __syncthreads_or(bad) != 0;
+    }
+  } else if (sel_here) {
+    // (the select's scratch lies in the position table, filled after it)
+    static_assert(sizeof(tk::LongSelSmem) <= sizeof(sm.rows) && sizeof(tk::WaveSelSmem) <= sizeof(sm.rows), "scratch");
+    bool done = sel_all;
     if (sel_all) {
       for (int u = tid; u < geo.n_sel; u += 64 * NWAVE) sm.sidx[u] = u;
-    } else {
+    } else if (sel_waves) {
+#pragma unroll
+      for (int j = 0; j < WPER; ++j) wkey[j] = tk::order_key(__uint_as_float(wkey[j]));
+      if constexpr (SEL > 2) {
+        done = tk::long_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::LongSelSmem*)sm.rows);
+      } else {
+        if (wave == 0) {
+          const bool ok = tk::wave_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx,
+                                               *(tk::WaveSelSmem*)sm.rows);
+          if (lane == 0) sm.sel_ok = ok;
+        }
+        lds_barrier();
+        done = sm.sel_ok != 0;
+      }
+    }
+    if (!done) {
+      // more units than the wave select takes, or too many ties: the radix select,
+      // SEL keys per thread (long rows filtered first; the filter declines, uniformly,
+      // when the bound it finds leaves more than a thread's worth of candidates)
+      constexpr int SK = SEL > 0 ? SEL : 1;
+      uint32_t skey[SK];
+#pragma unroll
+      for (int j = 0; j < SK; ++j) skey[j] = tk::order_key(srow[min(tid + j * tk::kThreads, geo.n_units - 1)]);
       auto valid = [&](int j) { return tid + j * tk::kThreads < geo.n_units; };
       auto index = [&](int j) { return tid + j * tk::kThreads; };
       uint32_t thr;
       int rem;
       bool ge;
-      // long rows: the filter first (it declines, uniformly, when the bound it
-      // finds leaves more than a thread's worth of candidates)
-      bool done = false;
       if constexpr (SEL > 2) done = geo.n_sel <= tk::kThreads && tk::filtered_select<SK>(skey, geo.n_units, geo.n_sel, sm.sidx);
       if (!done) {
         tk::radix_threshold<SK>(skey, valid, geo.n_sel, thr, rem, ge);
         tk::write_selection<SK>(skey, valid, index, thr, rem, ge, geo.n_sel, sm.sidx);
       }
     }
-    __syncthreads();
+    lds_barrier();
     if (sel_writer) {
       int32_t* orow = a.idx_out + (int64_t)bg * geo.idx_stride;
       for (int u = tid; u < geo.idx_stride; u += 64 * NWAVE) orow[u] = u < geo.n_sel ? sm.sidx[u] : -1;
     }
   }
-  const bool has_invalid = __syncthreads_or(bad) != 0;
 
   // Direct loads: instruction j of wave w fills LDS granules [(NI*w + j)*64, +64)
   // of the tile, lane l writing granule slot l; that slot belongs to tile row
@@ -331,7 +403,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
       if (w >= sel_len) {
         pos = geo.local_begin + (w - sel_len);
       } else {
-        const int u = w / geo.block_size;
+        const int u = div_by(w, a.d_block);
         const int bu = u < kSelLds ? sm.sidx[u] : idx_row[u];
         if (bu < 0 || bu >= geo.n_units) return kNoRow;
         pos = (int64_t)geo.unit_base + (int64_t)bu * geo.block_size + (w - u * geo.block_size);
@@ -372,8 +444,6 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   };
 
   // Byte offsets of this wave's 1 KB slices in the LDS tiles.
-  const uint32_t lds_k0 = (uint32_t)(uintptr_t)(INFLLM_LDS bf16_t*)sm.k[0];
-  const uint32_t lds_v0 = (uint32_t)(uintptr_t)(INFLLM_LDS bf16_t*)sm.v[0];
   const uint32_t lds_k = lds_k0 + NI * wave * 1024;
   const uint32_t lds_v = lds_v0 + NI * wave * 1024;
   constexpr uint32_t kTileBytes = KB * D * 2;
@@ -425,6 +495,43 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   // the derived addresses are formed per tile instead of held in registers)
   auto kaddr_of = [&](int kbuf) { return opaque_s(lds_k0 + kbuf * kTileBytes) + koff0; };
   auto vaddr_of = [&](int vbuf) { return opaque_s(lds_v0 + vbuf * kTileBytes) + voff0; };
+
+  // Q rows of this wave as the B operand (8 bf16 per lane per k-step), read back from
+  // their LDS rows like K fragments.  Under the remap the rows are turned in place
+  // first, by R(l_L) for a memory part and to their own positions for a local one:
+  // a lane takes one granule of one query and turns it for all of the query's heads,
+  // so that each angle's sine and cosine are formed once (per row and lane, with
+  // float64 angles, this took 4.5 us of a local part's prologue).
+  bf16x8 qreg[KSTEPS];
+  auto read_q = [&]() {
+    if (remap) {
+      const int gr = lane % CH, r_end = min(row0 + 32, R);
+      const int q_last = div_by(r_end - 1, a.d_group);
+      for (int q = div_by(row0, a.d_group) + lane / CH; q <= q_last; q += RPI) {
+        float cs[4], sn[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          cs[j] = mcos[j];
+          sn[j] = msin[j];
+          if (!mem_part) rope_cos_sin(rev[j], geo.past_len + q, cs[j], sn[j]);
+        }
+        for (int r = max(q * G, row0); r < min((q + 1) * G, r_end); ++r) {
+          INFLLM_LDS u32x4* at = (INFLLM_LDS u32x4*)(uintptr_t)(lds_q + (r - row0) * (2 * D) + 16 * (gr ^ swz<D>(r - row0)));
+          u32x4 raw = *at;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float x0 = __uint_as_float(raw[j] << 16), x1 = __uint_as_float(raw[j] & 0xFFFF0000u);
+            raw[j] = (uint32_t)f32_to_bf16(x0 * cs[j] - x1 * sn[j]) | ((uint32_t)f32_to_bf16(x0 * sn[j] + x1 * cs[j]) << 16);
+          }
+          *at = raw;
+        }
+      }
+      tk::wave_lds_fence();
+    }
+#pragma unroll
+    for (int s = 0; s < KSTEPS; ++s)
+      qreg[s] = *(const INFLLM_LDS bf16x8*)(uintptr_t)((lds_q + koff0) ^ (32u * s));
+  };
 
   f32x16 oacc[DBLK];
 #pragma unroll
@@ -513,6 +620,11 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   constexpr float kLazy = 65536.f;
   float lazy_bound = 0.f;  // 0 while m_run = -inf
   float neg_m = 0.f;       // -m_run, 0 while m_run = -inf
+  auto first_max = [&](float mx) {  // nothing accumulated yet
+    m_run = mx;
+    neg_m = (mx == -__builtin_inff()) ? 0.f : -mx;
+    lazy_bound = (mx == -__builtin_inff()) ? 0.f : kLazy;
+  };
   auto force_max = [&](float mx) {
     const float m_new = fmaxf(m_run, mx);
     const float alpha = (m_new == -__builtin_inff()) ? 1.f : fast_exp2(m_run - m_new);
@@ -782,36 +894,47 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   };
 
   if (t_begin < t_end) {
-    fill_rows(t_begin);
-    __syncthreads();
+    // K(t0) needs no table: its rows' positions directly, so that the load is on its
+    // way before the table is filled.
     TileOff off0, off1;
     {
-      uint32_t e0[NI], e1[NI], e2[NI];
-      row_read(t_begin, e0);
+      uint32_t e0[NI];
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        const uint32_t r = (uint32_t)(lrow0 + RPI * j);
+        e0[j] = group_row(t_begin * KB + (int)(r & ~gr_mask));
+      }
+      row_off(e0, off0);
+      note_valid(0, e0);
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) load_k(0, off0, j);
+    fill_rows(t_begin);
+    lds_barrier();
+    {
+      uint32_t e1[NI], e2[NI];
       row_read(t_begin + 1, e1);
       row_read(t_begin + 2, e2);
       row_read(t_begin + 3, e3);
       row_read(t_begin + 4, e4);
-      row_off(e0, off0);
       row_off(e1, off1);
       row_off(e2, off2);
       row_off(e3, off3);
       row_off(e4, off4);
-      note_valid(0, e0);
       note_valid(1, e1);
       note_valid(2, e2);
     }
 #pragma unroll
-    for (int j = 0; j < NI; ++j) load_k(0, off0, j);
+    for (int j = 0; j < NI; ++j) load_k(1, off1, j);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) load_k(2, off2, j);
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * NI));  // the query rows and K(t0) have landed
+    if (active) read_q();
+    lds_barrier();  // K(t0) published, the query rows read
 #pragma unroll
     for (int j = 0; j < NI; ++j) load_v(0, off0, j);
 #pragma unroll
-    for (int j = 0; j < NI; ++j) load_k(1, off1, j);
-#pragma unroll
     for (int j = 0; j < NI; ++j) load_v(1, off1, j);
-#pragma unroll
-    for (int j = 0; j < NI; ++j) load_k(2, off2, j);
-    publish_barrier<4 * NI>();  // K(t0) has landed
     if (!active) {
       int t = t_begin;
       for (; t + 2 < t_end; t += 2) {
@@ -839,7 +962,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
         for (int j = 0; j < 16; ++j)
           if (32 * kb + 8 * (j >> 2) + (j & 3) < lo) sA[kb][j] = -__builtin_inff();
     }
-    force_max(tile_max(sA));  // the first tile sets the running max
+    first_max(tile_max(sA));  // the first tile sets the running max
     l_pend = half_p(sA[0], p0);
 
     int t = t_begin;
@@ -943,30 +1066,36 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   {
     constexpr int CPR = kRowBytes / 16;  // 16-byte chunks per row
     const INFLLM_LDS char* stage = (const INFLLM_LDS char*)(const INFLLM_LDS bf16_t*)sm.k[0] + wave * 32 * kStageRow;
+    static_assert(CPR == CH, "a lane stores the rows it loaded");
+    // first row of the kv head's group: [G][n_q] rows of a partial, or of the output
     const int64_t rows_total = (int64_t)a.batch * a.n_q_heads * geo.n_q;
+    const int64_t head0 = b * a.n_q_heads + g * G;
+    char* base = one_part ? (char*)a.out + head0 * a.out_head_stride * 2
+                          : (char*)a.part_o + ((int64_t)part * rows_total + head0 * geo.n_q) * kRowBytes;
+    const int64_t hstride = one_part ? a.out_head_stride * 2 : (int64_t)geo.n_q * kRowBytes;
+    int i = li0, h = lh0;
 #pragma unroll
     for (int k = 0; k < 32 * CPR / 64; ++k) {
-      const int c = 64 * k + lane, r = c / CPR, ch = c % CPR;
-      const int row = rt * ROWS_WG + wave * 32 + r;
-      if (row >= R) continue;
+      const int r = RPI * k + lane / CH, ch = lane % CH;
       const u32x4 w = *(const INFLLM_LDS u32x4*)(stage + r * kStageRow + ch * 16);
-      const int ri = row / G, rh = g * G + (row - ri * G);
-      char* dst;
-      if (one_part)
-        dst = (char*)a.out + ((int64_t)(b * a.n_q_heads + rh) * a.out_head_stride + (int64_t)ri * D) * 2;
-      else
-        dst = (char*)a.part_o + ((int64_t)part * rows_total + (int64_t)(b * a.n_q_heads + rh) * geo.n_q + ri) * kRowBytes;
-      *(u32x4*)(dst + ch * 16) = w;
+      if (active && row0 + r < R) *(u32x4*)(base + h * hstride + (int64_t)i * kRowBytes + ch * 16) = w;
+      next_row(i, h);
     }
   }
 }
 
 }  // namespace
 
-hipError_t launch_attend_mfma(const AttendArgs& a, hipStream_t s) {
+hipError_t launch_attend_mfma(const AttendArgs& args, hipStream_t s) {
+  AttendArgs a = args;
   const int G = a.n_q_heads / a.n_kv_heads;
   const int R = G * a.geom.n_q;
-  const int n_row_tiles = (R + ROWS_WG - 1) / ROWS_WG;
+  const int n_row_tiles = (R + 32 * a.row_waves - 1) / (32 * a.row_waves);
+  a.d_row_tiles = fast_div(n_row_tiles);
+  a.d_parts = fast_div(a.parts);
+  a.d_kv = fast_div(a.n_kv_heads);
+  a.d_group = fast_div(G);
+  a.d_block = fast_div(a.geom.block_size);
   const int blocks = n_row_tiles * a.parts * a.batch * a.n_kv_heads;
   const dim3 grid(blocks), block(64 * NWAVE);
   const bool sel = a.idx_out != nullptr, mass = sel && a.mass_part != nullptr;

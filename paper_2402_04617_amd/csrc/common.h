@@ -72,6 +72,22 @@ __device__ __forceinline__ int64_t virtual_pos(const StepGeom& g, const int32_t*
   return g.local_begin + (w - sel_len);
 }
 
+// Division by a number the host knows (1 <= d < 2^31): one high multiply and a
+// correction in place of the 20-instruction sequence of a general division.
+struct FastDiv {
+  uint32_t d, mul;
+};
+__host__ inline FastDiv fast_div(int d) {
+  return FastDiv{(uint32_t)d, d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d) + 1u};
+}
+// n / d for 0 <= n < 2^31: mul = floor(2^32 / d) + 1 gives the quotient or one more.
+__device__ __forceinline__ int div_by(int n, const FastDiv& f) {
+  if (f.mul == 0) return n;
+  uint32_t q = __umulhi((uint32_t)n, f.mul);
+  q -= q * f.d > (uint32_t)n ? 1u : 0u;
+  return (int)q;
+}
+
 // Positional remap (Section 3.2, "Positional Encoding"): rotary tables for a
 // step whose q and k arrive without positions.  Dimension pair i = (2i, 2i+1)
 // turns by the angle p * theta_i.  Keys of I and of the memory units are kept
@@ -80,20 +96,26 @@ __device__ __forceinline__ int64_t virtual_pos(const StepGeom& g, const int32_t*
 constexpr int kMaxPairs = 64;  // D/2 at D = 128
 struct RopeArgs {
   int32_t on;                // 0: positions pre-applied, nothing is rotated
-  double rev[kMaxPairs];     // theta_i / (2 pi): revolutions per position of pair i
+  uint64_t rev[kMaxPairs];   // theta_i / (2 pi) mod 1 in units of 2^-64: revolutions per position of pair i
   float mem_cos[kMaxPairs];  // cos(l_L theta_i)
   float mem_sin[kMaxPairs];  // sin(l_L theta_i)
 };
 
-// cos and sin of p * theta_i.  The angle is reduced to [0, 1) revolutions in
-// float64 (p * theta_i reaches 10^6 radians at a million positions); the
-// hardware sine and cosine take revolutions.
-__device__ __forceinline__ void rope_cos_sin(const RopeArgs& r, int64_t pos, int i, float& c, float& s) {
-  double t = (double)pos * r.rev[i];
-  t -= floor(t);
-  const float f = (float)t;
+// cos and sin of p * theta_i, rev = r.rev[i].  Whole revolutions drop out of the
+// fixed-point product by itself: its top 32 fraction bits are two 32-bit multiplies
+// (positions fit 32 bits: the store holds them all), within 2^-32 + p * 2^-65
+// revolutions of the exact angle -- closer than a float64 product at a million
+// positions, and several times cheaper.  The hardware sine and cosine take
+// revolutions.
+__device__ __forceinline__ void rope_cos_sin(uint64_t rev, int64_t pos, float& c, float& s) {
+  const uint32_t p = (uint32_t)pos;
+  const uint32_t t = __umulhi(p, (uint32_t)rev) + p * (uint32_t)(rev >> 32);
+  const float f = (float)t * 0x1p-32f;
   s = __builtin_amdgcn_sinf(f);
   c = __builtin_amdgcn_cosf(f);
+}
+__device__ __forceinline__ void rope_cos_sin(const RopeArgs& r, int64_t pos, int i, float& c, float& s) {
+  rope_cos_sin(r.rev[i], pos, c, s);
 }
 
 // XCD-aware workgroup order: consecutive logical ids land on the same XCD (and so

@@ -124,9 +124,9 @@ struct TopkRows {
 hipError_t launch_select_topk_var(int rows, const float* scores, int stride, int n_max, const TopkRows& tr, int k,
                                   int32_t* idx, hipStream_t s);
 
-// Query rows per workgroup of the bf16 matrix-core attention kernel, and the
-// workgroup count the part chooser aims for (one per compute unit).
-constexpr int kMfmaRowsPerWg = 256;
+// Waves of 32 query rows in a workgroup of the bf16 matrix-core attention kernel,
+// and the workgroups that run at a time (one per compute unit).
+constexpr int kMfmaWaves = 8;
 constexpr int kMfmaTargetWgs = 256;
 // Workgroups the bf16 decode kernel aims for (two per compute unit), and the
 // fewest keys it gives one workgroup.
@@ -191,6 +191,10 @@ struct AttendArgs {
   float* part_lse;     // [parts][rows]
   int32_t* part_exp;   // [parts][rows] (bf16 only)
   int parts;
+  // Matrix-core kernel: waves of a workgroup that hold query rows (8, or 4 where the
+  // rows are too few to fill the chip with 8); its launcher fills the divisors.
+  int row_waves;
+  FastDiv d_row_tiles, d_parts, d_kv, d_group, d_block;
   bool bf16;
 };
 // The step of sequence b as a kernel sees it.
@@ -212,9 +216,10 @@ __host__ __device__ inline SeqStep seq_step(const AttendArgs& a, int b) {
   r.parts_mem = a.rope.on ? split_parts_mem(a.parts, r.mem_len, r.geom.n_virtual) : 0;
   return r;
 }
-// Number of key parts the attention uses for this shape, limited by max_parts.
+// Number of key parts the attention uses for this shape, limited by max_parts, and
+// for the matrix-core kernel the waves of a workgroup that hold rows.
 int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int n_q, int n_sel, int n_virtual,
-                        int max_parts);
+                        int max_parts, int* row_waves);
 hipError_t launch_attend(const AttendArgs& a, hipStream_t s);
 // Whether launch_attend runs the matrix-core kernel for these arguments.
 bool attend_uses_mfma(const AttendArgs& a);

@@ -1,6 +1,6 @@
 // Top-k unit lookup (Section 3.2: only the k_m units of highest relevance are loaded).
 //
-// One workgroup per row running the radix select of topk_select.h.
+// One workgroup per row running a select of topk_select.h.
 #include "topk_select.h"
 
 namespace infllm {
@@ -27,6 +27,35 @@ __global__ void __launch_bounds__(kThreads) topk_kernel(const float* __restrict_
   __shared__ int wave_tot[kWaves];
   if constexpr (PER > 0) {
     if (k_eff < n) {
+      // up to kWaveK units: the first wave alone (rows of up to 1,024 scores), or the
+      // waves' candidates reduced once more (longer rows); the radix select otherwise,
+      // and where too many scores tie
+      if (k_eff <= tk::kWaveK) {
+        constexpr int WPER = 16;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        __shared__ union {
+          tk::WaveSelSmem one;
+          tk::LongSelSmem all;
+        } sel;
+        __shared__ int ok;
+        uint32_t key[WPER];
+        if (PER > 2 || wave == 0) {
+#pragma unroll
+          for (int j = 0; j < WPER; ++j) key[j] = tk::order_key(s[min(wave * 64 * WPER + 64 * j + lane, n - 1)]);
+        }
+        bool done;
+        if constexpr (PER > 2) {
+          done = tk::long_select<WPER>(key, n, k_eff, out, sel.all);
+        } else {
+          if (wave == 0) {
+            const bool r = tk::wave_select<WPER>(key, n, k_eff, out, sel.one);
+            if (lane == 0) ok = r;
+          }
+          __syncthreads();
+          done = ok != 0;
+        }
+        if (done) return;
+      }
       tk::radix_select_reg<PER>(s, n, k_eff, out);
       return;
     }

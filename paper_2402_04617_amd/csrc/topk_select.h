@@ -343,6 +343,190 @@ __device__ bool filtered_select(const uint32_t (&key)[PER], int n, int k_eff, in
   return true;
 }
 
+// ---- selection by single waves ----------------------------------------------
+// For k_eff <= kWaveK.  A wave holds up to 64*PER keys, PER per lane; the k-th
+// largest of the 64 lane maxima (lanes without a key hold 0) is a bound with at
+// least k keys at or above it, found bit by bit with ballots.  The few keys at or
+// above the bound (about 1.4 k for random scores) are compacted in index order and
+// rank themselves by counting.  No histogram, no atomics, no barrier: in the
+// attention's prologue, where the whole workgroup waits for the lookup, 32 of 987
+// scores are loaded and selected in 2.9 us where the radix select of eight waves
+// took 4.6 (8,155 scores, by all waves: 12.3 -> 6.1 us); as a launch of its own
+// 4.5 -> 4.0 us (7.1 -> 6.1).
+constexpr int kWaveK = 48;      // most units selected this way (at 64 the bound is the smallest lane maximum,
+                                // which leaves too many candidates: 6.2 against 4.4 us at 987 scores)
+constexpr int kWaveCand = 128;  // most candidates a wave ranks
+
+// A bound T on the k-th largest lane value: at least k of the 64 values are >= T
+// (its low bits are zero; 0 when fewer than k values are nonzero).
+__device__ __forceinline__ uint32_t lane_bound(uint32_t mx, int k) {
+  uint32_t T = 0;
+#pragma unroll
+  for (int s = 30; s >= 16; s -= 2) {
+    const uint32_t t1 = T | (1u << s), t2 = T | (2u << s), t3 = T | (3u << s);
+    const int c1 = __popcll(__ballot(mx >= t1)), c2 = __popcll(__ballot(mx >= t2)), c3 = __popcll(__ballot(mx >= t3));
+    T = c3 >= k ? t3 : c2 >= k ? t2 : c1 >= k ? t1 : T;
+  }
+  return T;
+}
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Candidates in index order: key + 1 (never 0; slots past the last hold 0) and the
+// element's index.  One slot past the end takes the writes of non-candidates.
+template <int CAP>
+struct Candidates {
+  __attribute__((aligned(16))) uint32_t key[CAP + 4];
+  int32_t idx[CAP + 4];
+};
+
+// The k largest of n_cand <= kWaveCand candidates (this wave's own writes), ties to
+// the earlier one, ascending to out.
+template <int CAP>
+__device__ __forceinline__ void rank_candidates(const Candidates<CAP>& cd, int n_cand, int k, int32_t* __restrict__ out) {
+  const int l = threadIdx.x & 63;
+  const uint32_t k0 = cd.key[l], k1 = l + 64 < n_cand ? cd.key[l + 64] : 0u;
+  const int i0 = cd.idx[l], i1 = cd.idx[min(l + 64, n_cand)];
+  // four candidates per (broadcast) read; slots past the last hold 0 and count for nobody
+  int r0 = 0, r1 = 0;
+  for (int c = 0; c < n_cand; c += 4) {
+    const u32x4 kc = *(const u32x4*)&cd.key[c];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      r0 += kc[e] > k0 ? 1 : 0;
+      r1 += kc[e] > k1 ? 1 : 0;
+    }
+  }
+  bool keep0 = l < n_cand && r0 < k, keep1 = l + 64 < n_cand && r1 < k;
+  unsigned long long m0 = __ballot(keep0), m1 = __ballot(keep1);
+  if (__popcll(m0) + __popcll(m1) != k) {
+    // equal keys straddle the k-th place: count the earlier ones too
+    for (int c = 0; c < n_cand; ++c) {
+      const uint32_t kc = cd.key[c];
+      r0 += (kc == k0 && c < l) ? 1 : 0;
+      r1 += (kc == k1 && c < l + 64) ? 1 : 0;
+    }
+    keep0 = l < n_cand && r0 < k;
+    keep1 = l + 64 < n_cand && r1 < k;
+    m0 = __ballot(keep0);
+    m1 = __ballot(keep1);
+  }
+  if (keep0) out[lanes_below(m0)] = i0;
+  if (keep1) out[__popcll(m0) + lanes_below(m1)] = i1;
+}
+
+// Writes the keys >= T of this wave's elements (element j of lane l has index
+// ix(j); ascending in (j, l)) from slot `base` on, and returns the slot after.
+template <int PER, int CAP, typename Valid, typename Index>
+__device__ __forceinline__ int compact_candidates(const uint32_t (&key)[PER], Valid valid, Index ix, uint32_t T, int base,
+                                                  Candidates<CAP>& cd) {
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const bool c = valid(j) && key[j] >= T;
+    const unsigned long long m = __ballot(c);
+    const int slot = c ? min(base + lanes_below(m), CAP + 3) : CAP + 3;
+    cd.key[slot] = key[j] + 1u;
+    cd.idx[slot] = ix(j);
+    base += __popcll(m);
+  }
+  return base;
+}
+template <int PER, typename Valid>
+__device__ __forceinline__ uint32_t lane_max(const uint32_t (&key)[PER], Valid valid) {
+  uint32_t mx = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) mx = max(mx, valid(j) ? key[j] : 0u);
+  return mx;
+}
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// One wave: the k_eff largest of n <= 64*PER keys (lane l: element l + 64*j),
+// 0 < k_eff <= kWaveK, k_eff < n.  False (wave-uniform) when too many keys tie at
+// the bound; nothing is written then.
+typedef Candidates<kWaveCand> WaveSelSmem;
+template <int PER>
+__device__ __forceinline__ bool wave_select(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out,
+                                            WaveSelSmem& sm) {
+  const int l = threadIdx.x & 63;
+  auto valid = [&](int j) { return l + 64 * j < n; };
+  const uint32_t T = lane_bound(lane_max<PER>(key, valid), k_eff);
+#pragma unroll
+  for (int j = 0; j < kWaveCand; j += 64) sm.key[j + l] = 0u;
+  wave_lds_fence();
+  const int n_cand = compact_candidates<PER>(key, valid, [&](int j) { return l + 64 * j; }, T, 0, sm);
+  if (n_cand > kWaveCand) return false;
+  wave_lds_fence();
+  rank_candidates(sm, n_cand, k_eff, out);
+  return true;
+}
+
+// The whole workgroup (kThreads): rows of up to kThreads*kMaxPer keys, wave w
+// holding elements [w*64*PER, (w+1)*64*PER), element l + 64*j of them in lane l.
+// The waves' bounds (the largest still has k keys at or above it) leave a few
+// hundred candidates, which the first wave reduces once more and ranks.  False
+// (workgroup-uniform) when too many keys tie.  Ends with a barrier.
+constexpr int kLongCand = 512;
+struct LongSelSmem {
+  Candidates<kLongCand> all;
+  WaveSelSmem last;
+  uint32_t bound[kWaves];
+  int count[kWaves];
+  int ok;
+};
+template <int PER>
+__device__ __forceinline__ bool long_select(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out,
+                                            LongSelSmem& sm) {
+  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int e0 = wave * 64 * PER + l;
+  auto valid = [&](int j) { return e0 + 64 * j < n; };
+  const uint32_t Tw = lane_bound(lane_max<PER>(key, valid), k_eff);
+  if (l == 0) sm.bound[wave] = Tw;
+  __syncthreads();
+  uint32_t T = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) T = max(T, sm.bound[w]);
+  int c = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) c += __popcll(__ballot(valid(j) && key[j] >= T));
+  if (l == 0) sm.count[wave] = c;
+  __syncthreads();
+  int base = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    base += w < wave ? sm.count[w] : 0;
+    total += sm.count[w];
+  }
+  if (total > kLongCand) return false;
+  compact_candidates<PER>(key, valid, [&](int j) { return e0 + 64 * j; }, T, base, sm.all);
+  __syncthreads();
+  if (wave == 0) {
+    constexpr int P2 = kLongCand / 64;
+    uint32_t k2[P2];
+    int32_t i2[P2];
+    auto valid2 = [&](int j) { return l + 64 * j < total; };
+#pragma unroll
+    for (int j = 0; j < P2; ++j) {
+      k2[j] = valid2(j) ? sm.all.key[l + 64 * j] - 1u : 0u;
+      i2[j] = sm.all.idx[l + 64 * j];
+    }
+    const uint32_t T2 = max(T, lane_bound(lane_max<P2>(k2, valid2), k_eff));
+#pragma unroll
+    for (int j = 0; j < kWaveCand; j += 64) sm.last.key[j + l] = 0u;
+    wave_lds_fence();
+    const int n2 = compact_candidates<P2>(k2, valid2, [&](int j) { return i2[j]; }, T2, 0, sm.last);
+    wave_lds_fence();
+    if (n2 <= kWaveCand) rank_candidates(sm.last, n2, k_eff, out);
+    if (l == 0) sm.ok = n2 <= kWaveCand;
+  }
+  __syncthreads();
+  return sm.ok != 0;
+}
+
 // Common path: the radix select with the row's keys held in registers (thread
 // t: keys t, t + kThreads, ...; read once); rows of 4+ keys per thread try the
 // filter above first.
