@@ -723,12 +723,19 @@ static infllm_status step_impl(const infllm_params* p, const infllm_memory* m, c
   // The append also yields the chunk's group-query sums, which scoring consumes
   // directly: the scan total, or with the mean representation (no scan) the
   // partial sums of its query-sum blocks.
+  // With a few tokens and no units to build, append and scoring are one launch.
   float* qbar = (float*)workspace;
   const int qbar_parts = mean ? score_qbar_parts(p->n_q_heads / p->n_kv_heads, n_q) : 1;
-  if ((st = launch_status(launch_append(aa, s, part.n_units > 0 ? qbar : nullptr, fuse ? &ba : nullptr))) !=
-      INFLLM_OK)
+  const bool thin = n_q > 0 && n_q <= kThinAppend && ba.n_new == 0 && part.n_units > 0;
+  if (thin) {
+    if (remap(p)) aa.rope = at.rope;  // both tables
+    const ThinScoreArgs ts = {m->unit_ksum, scores, m->max_units, part.n_units, p->block_size, part.n_units};
+    if ((st = launch_status(launch_append_score(aa, ts, s))) != INFLLM_OK) return st;
+  } else if ((st = launch_status(launch_append(aa, s, part.n_units > 0 ? qbar : nullptr, fuse ? &ba : nullptr))) !=
+             INFLLM_OK) {
     return st;
-  if (part.n_units > 0) {
+  }
+  if (part.n_units > 0 && !thin) {
     sa.qbar_parts = qbar;
     if (n_q == 0) {
       if ((st = launch_status(launch_score(sa, s))) != INFLLM_OK) return st;
@@ -736,12 +743,11 @@ static infllm_status step_impl(const infllm_params* p, const infllm_memory* m, c
       return st;
     }
   }
-  // The matrix-core attention selects the units itself (one launch fewer on the
-  // step's critical path) when the score rows are short enough for its prologue;
+  // The attention selects the units itself (one launch fewer on the step's critical
+  // path) when the score rows are short enough for its prologue;
   // otherwise the selection kernel runs first.  With no units yet either of them
   // writes the -1 padding of idx.
-  const bool select_in_attend =
-      p->topk > 0 && p->topk <= kFusedSelectMaxK && part.n_units <= kFusedSelectMax && attend_uses_mfma(at);
+  const bool select_in_attend = p->topk > 0 && part.n_units <= attend_select_max(at);
   if (select_in_attend) {
     at.sel_scores = scores;
     at.sel_stride = part.n_units;
@@ -754,7 +760,8 @@ static infllm_status step_impl(const infllm_params* p, const infllm_memory* m, c
   // With the unit mass asked for and the lookup inside the attention, the
   // attention also writes each unit tile's per-row sums of P; one small launch
   // after the merge turns them into the masses (else the unit-mass kernel).
-  const bool mass_in_attend = mr != nullptr && !mass_skip && select_in_attend && mass_area != nullptr;
+  const bool mass_in_attend =
+      mr != nullptr && !mass_skip && select_in_attend && attend_uses_mfma(at) && mass_area != nullptr;
   if (mass_in_attend) {
     at.mass_part = (float2*)mass_area;
     at.mass_tiles = p->topk * (p->block_size / 64);
@@ -892,10 +899,16 @@ infllm_status infllm_step_varlen(const infllm_params* p, const infllm_memory* m,
   if (new_max > 0 && !fuse && (st = launch_status(launch_build_units(ba, s))) != INFLLM_OK) return st;
   float* qbar = (float*)workspace;
   const int qbar_parts = mean ? score_qbar_parts(p->n_q_heads / p->n_kv_heads, n_q) : 1;
-  if ((st = launch_status(launch_append(aa, s, n_units_max > 0 ? qbar : nullptr,
-                                        (fuse && new_max > 0) ? &ba : nullptr))) != INFLLM_OK)
+  const bool thin = n_q > 0 && n_q <= kThinAppend && new_max == 0 && n_units_max > 0;
+  if (thin) {
+    if (remap(p)) aa.rope = at.rope;  // both tables
+    const ThinScoreArgs ts = {m->unit_ksum, scores, m->max_units, n_units_max, p->block_size, m->max_units};
+    if ((st = launch_status(launch_append_score(aa, ts, s))) != INFLLM_OK) return st;
+  } else if ((st = launch_status(launch_append(aa, s, n_units_max > 0 ? qbar : nullptr,
+                                               (fuse && new_max > 0) ? &ba : nullptr))) != INFLLM_OK) {
     return st;
-  if (n_units_max > 0) {
+  }
+  if (n_units_max > 0 && !thin) {
     sa.qbar_parts = qbar;
     if (n_q == 0) {
       if ((st = launch_status(launch_score(sa, s))) != INFLLM_OK) return st;
@@ -905,7 +918,7 @@ infllm_status infllm_step_varlen(const infllm_params* p, const infllm_memory* m,
   }
   // As in infllm_step: the attention selects each sequence's units itself when
   // every score row is short enough (a sequence without units gets -1 padding).
-  if (p->topk > 0 && p->topk <= kFusedSelectMaxK && n_units_max <= kFusedSelectMax && attend_uses_mfma(at)) {
+  if (p->topk > 0 && n_units_max <= attend_select_max(at)) {
     at.sel_scores = scores;
     at.sel_stride = m->max_units;
     at.sel_units = n_units_max;

@@ -159,6 +159,126 @@ struct AppendGrid {
   int n_copy_per_head;  // copy blocks per (sequence, kv head)
 };
 
+// Copy role, block blk.
+template <typename T, bool ROPE>
+__device__ __forceinline__ void copy_block(const AppendArgs& a, int blk, int n_copy_per_head) {
+  const int D = a.head_dim;
+  // ---- copy role: K and V rows of the chunk into the store; each thread
+  // moves kCopyPerThread 16-byte vectors of one (sequence, kv head).
+  constexpr int VEC = 16 / sizeof(T);
+  const int vec_per_head = a.n_q * D / VEC;
+  const int64_t head = blk / n_copy_per_head;
+  const int cblk = blk % n_copy_per_head;
+  const int64_t past = seq_past(a, (int)(head / a.n_kv_heads));
+  const uint4* src_k = (const uint4*)a.k_src + head * (a.kv_head_stride / VEC);
+  const uint4* src_v = (const uint4*)a.v_src + head * (a.kv_head_stride / VEC);
+  uint4* dst_k = (uint4*)a.k_store + head * (a.capacity * D / VEC) + past * D / VEC;
+  uint4* dst_v = (uint4*)a.v_store + head * (a.capacity * D / VEC) + past * D / VEC;
+  const int base = cblk * kThreads * kCopyPerThread + threadIdx.x;
+  // all loads first (clamped indices), then the guarded stores
+  const int e0 = base, e1 = base + kThreads, e2 = base + 2 * kThreads, e3 = base + 3 * kThreads;
+  static_assert(kCopyPerThread == 4, "copy role moves four vectors per thread");
+  const int last = vec_per_head - 1;
+  const uint4 k0 = src_k[min(e0, last)], k1 = src_k[min(e1, last)], k2 = src_k[min(e2, last)],
+              k3 = src_k[min(e3, last)];
+  const uint4 v0 = src_v[min(e0, last)], v1 = src_v[min(e1, last)], v2 = src_v[min(e2, last)],
+              v3 = src_v[min(e3, last)];
+  if (e0 < vec_per_head) { dst_k[e0] = k0; dst_v[e0] = v0; }
+  if (e1 < vec_per_head) { dst_k[e1] = k1; dst_v[e1] = v1; }
+  if (e2 < vec_per_head) { dst_k[e2] = k2; dst_v[e2] = v2; }
+  if (e3 < vec_per_head) { dst_k[e3] = k3; dst_v[e3] = v3; }
+  if (ROPE) {
+    // positional remap: the keys rotated to their own positions go to k_rot
+    uint4* dst_r = (uint4*)a.k_rot + head * (a.capacity * D / VEC) + past * D / VEC;
+    const int vpp = D / VEC;  // vectors per position
+    auto rot = [&](int e, const uint4& w) {
+      if (e < vec_per_head)
+        dst_r[e] = rotate_vec<T>(w, past + e / vpp, (e % vpp) * (VEC / 2), a.rope);
+    };
+    rot(e0, k0);
+    rot(e1, k1);
+    rot(e2, k2);
+    rot(e3, k3);
+  }
+}
+
+// Thin scan role, block blk.
+template <typename T, int GT, bool ROPE>
+__device__ __forceinline__ void thin_scan_block(const AppendArgs& a, int blk, float* __restrict__ qbar) {
+  const int D = a.head_dim;
+      // ---- thin scan role, for chunks of at most kThinMaxQ positions (decoding):
+      // one thread per (sequence*kv head, dim) walks the positions in order.  The
+      // 16 threads of a slice are adjacent lanes, so the partial score of a slice
+      // is a 16-lane sum.
+      const int gid = blk * kThreads + threadIdx.x;
+      if (gid >= a.batch * a.n_kv_heads * D) return;  // whole waves: the total is a multiple of 64
+      const int bg = gid / D, d = gid - bg * D;
+      const int b = bg / a.n_kv_heads, g = bg - b * a.n_kv_heads;
+      const int64_t past = seq_past(a, b);
+      const int G = GT > 0 ? GT : a.n_q_heads / a.n_kv_heads;
+      const T* qb = (const T*)a.q + (int64_t)(b * a.n_q_heads + g * G) * a.q_head_stride + d;
+      double* col = a.qprefix + (int64_t)bg * a.ring * D + d;
+      const int slot0 = (int)(past % a.ring);
+      // every load that does not depend on this launch's writes is issued first
+      const T* kread = (const T*)a.k_store;
+      double x[kThinMaxQ], ht[kThinMaxQ];
+      float kt[kThinMaxQ];
+  #pragma unroll
+      for (int i = 0; i < kThinMaxQ; ++i) {
+        x[i] = 0.0;
+        ht[i] = 0.0;
+        kt[i] = 0.f;
+        if (i < a.n_q) {
+          for (int h = 0; h < G; ++h) x[i] += (double)Elem<T>::load(qb + h * a.q_head_stride + (int64_t)i * D);
+          const int64_t t = past + i - a.n_local;
+          if (t >= a.n_init && t < past) {
+            const int sp = slot0 + i - (slot0 + i >= a.ring ? a.ring : 0);
+            const int st = sp - a.n_local + (sp < a.n_local ? a.ring : 0);  // n_local < ring
+            ht[i] = col[(int64_t)st * D];
+            kt[i] = Elem<T>::load(kread + ((int64_t)bg * a.capacity + t) * D + d);
+          }
+        }
+      }
+      double run = 0.0;
+      if (past > 0) run = col[(int64_t)(slot0 == 0 ? a.ring - 1 : slot0 - 1) * D];
+      const double base = run;
+      float raw_tot = 0.f;  // the chunk's unrotated query sum (remap: the ring holds rotated sums)
+      // R(pos) on dimension d of a pair split over lanes d, d^1 (uniform branch: pos is per position)
+      auto rot_lane = [&](double v, int64_t pos) -> double {
+        const double w = __shfl_xor(v, 1);
+        float c, sn;
+        rope_cos_sin(a.rope, pos, d >> 1, c, sn);
+        return (d & 1) ? w * (double)sn + v * (double)c : v * (double)c - w * (double)sn;
+      };
+  #pragma unroll
+      for (int i = 0; i < kThinMaxQ; ++i) {
+        if (i >= a.n_q) continue;  // (not break: the loop stays unrolled, the arrays in registers)
+        raw_tot += (float)x[i];
+        if (ROPE) x[i] = rot_lane(x[i], past + i);
+        run += x[i];
+        const int sp = slot0 + i - (slot0 + i >= a.ring ? a.ring : 0);
+        col[(int64_t)sp * D] = run;
+        const int64_t t = past + i - a.n_local;
+        if (t >= a.n_init) {
+          double h = ht[i], k = kt[i];
+          if (t >= past) {
+            // token of this chunk: its running sum was written by this thread above
+            const int st = sp - a.n_local + (sp < a.n_local ? a.ring : 0);
+            h = col[(int64_t)st * D];
+            k = Elem<T>::load((const T*)a.k_src + (int64_t)bg * a.kv_head_stride + (t - past) * D + d);
+          }
+          // positional remap: the input key turned to its own position, unrounded
+          if (ROPE) k = rot_lane(k, t);
+          double part = k * (run - h);
+  #pragma unroll
+          for (int o = 1; o < kRpartDims; o <<= 1) part += __shfl_xor(part, o);
+          if ((d % kRpartDims) == 0)
+            a.rpart[((int64_t)bg * (D / kRpartDims) + d / kRpartDims) * a.ring + (int)(t % a.ring)] = part;
+        }
+      }
+      if (qbar != nullptr) qbar[(int64_t)bg * D + d] = ROPE ? raw_tot : (float)(run - base);
+}
+
 // GT: the query group size G when known at compile time (0: read it at run time).
 // ROPE: the positional remap is on (a.rope.on), fixed at compile time so that
 // the plain path carries none of its code.
@@ -185,119 +305,12 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
   }
   blk -= grid.n_qsum;
   if (blk >= grid.n_scan) {
-    // ---- copy role: K and V rows of the chunk into the store; each thread
-    // moves kCopyPerThread 16-byte vectors of one (sequence, kv head).
-    blk -= grid.n_scan;
-    constexpr int VEC = 16 / sizeof(T);
-    const int vec_per_head = a.n_q * D / VEC;
-    const int64_t head = blk / grid.n_copy_per_head;
-    const int cblk = blk % grid.n_copy_per_head;
-    const int64_t past = seq_past(a, (int)(head / a.n_kv_heads));
-    const uint4* src_k = (const uint4*)a.k_src + head * (a.kv_head_stride / VEC);
-    const uint4* src_v = (const uint4*)a.v_src + head * (a.kv_head_stride / VEC);
-    uint4* dst_k = (uint4*)a.k_store + head * (a.capacity * D / VEC) + past * D / VEC;
-    uint4* dst_v = (uint4*)a.v_store + head * (a.capacity * D / VEC) + past * D / VEC;
-    const int base = cblk * kThreads * kCopyPerThread + threadIdx.x;
-    // all loads first (clamped indices), then the guarded stores
-    const int e0 = base, e1 = base + kThreads, e2 = base + 2 * kThreads, e3 = base + 3 * kThreads;
-    static_assert(kCopyPerThread == 4, "copy role moves four vectors per thread");
-    const int last = vec_per_head - 1;
-    const uint4 k0 = src_k[min(e0, last)], k1 = src_k[min(e1, last)], k2 = src_k[min(e2, last)],
-                k3 = src_k[min(e3, last)];
-    const uint4 v0 = src_v[min(e0, last)], v1 = src_v[min(e1, last)], v2 = src_v[min(e2, last)],
-                v3 = src_v[min(e3, last)];
-    if (e0 < vec_per_head) { dst_k[e0] = k0; dst_v[e0] = v0; }
-    if (e1 < vec_per_head) { dst_k[e1] = k1; dst_v[e1] = v1; }
-    if (e2 < vec_per_head) { dst_k[e2] = k2; dst_v[e2] = v2; }
-    if (e3 < vec_per_head) { dst_k[e3] = k3; dst_v[e3] = v3; }
-    if (ROPE) {
-      // positional remap: the keys rotated to their own positions go to k_rot
-      uint4* dst_r = (uint4*)a.k_rot + head * (a.capacity * D / VEC) + past * D / VEC;
-      const int vpp = D / VEC;  // vectors per position
-      auto rot = [&](int e, const uint4& w) {
-        if (e < vec_per_head)
-          dst_r[e] = rotate_vec<T>(w, past + e / vpp, (e % vpp) * (VEC / 2), a.rope);
-      };
-      rot(e0, k0);
-      rot(e1, k1);
-      rot(e2, k2);
-      rot(e3, k3);
-    }
+    copy_block<T, ROPE>(a, blk - grid.n_scan, grid.n_copy_per_head);
     return;
   }
 
   if (grid.thin) {
-    // ---- thin scan role, for chunks of at most kThinMaxQ positions (decoding):
-    // one thread per (sequence*kv head, dim) walks the positions in order.  The
-    // 16 threads of a slice are adjacent lanes, so the partial score of a slice
-    // is a 16-lane sum.
-    const int gid = blk * kThreads + threadIdx.x;
-    if (gid >= a.batch * a.n_kv_heads * D) return;  // whole waves: the total is a multiple of 64
-    const int bg = gid / D, d = gid - bg * D;
-    const int b = bg / a.n_kv_heads, g = bg - b * a.n_kv_heads;
-    const int64_t past = seq_past(a, b);
-    const int G = GT > 0 ? GT : a.n_q_heads / a.n_kv_heads;
-    const T* qb = (const T*)a.q + (int64_t)(b * a.n_q_heads + g * G) * a.q_head_stride + d;
-    double* col = a.qprefix + (int64_t)bg * a.ring * D + d;
-    const int slot0 = (int)(past % a.ring);
-    // every load that does not depend on this launch's writes is issued first
-    const T* kread = (const T*)a.k_store;
-    double x[kThinMaxQ], ht[kThinMaxQ];
-    float kt[kThinMaxQ];
-#pragma unroll
-    for (int i = 0; i < kThinMaxQ; ++i) {
-      x[i] = 0.0;
-      ht[i] = 0.0;
-      kt[i] = 0.f;
-      if (i < a.n_q) {
-        for (int h = 0; h < G; ++h) x[i] += (double)Elem<T>::load(qb + h * a.q_head_stride + (int64_t)i * D);
-        const int64_t t = past + i - a.n_local;
-        if (t >= a.n_init && t < past) {
-          const int sp = slot0 + i - (slot0 + i >= a.ring ? a.ring : 0);
-          const int st = sp - a.n_local + (sp < a.n_local ? a.ring : 0);  // n_local < ring
-          ht[i] = col[(int64_t)st * D];
-          kt[i] = Elem<T>::load(kread + ((int64_t)bg * a.capacity + t) * D + d);
-        }
-      }
-    }
-    double run = 0.0;
-    if (past > 0) run = col[(int64_t)(slot0 == 0 ? a.ring - 1 : slot0 - 1) * D];
-    const double base = run;
-    float raw_tot = 0.f;  // the chunk's unrotated query sum (remap: the ring holds rotated sums)
-    // R(pos) on dimension d of a pair split over lanes d, d^1 (uniform branch: pos is per position)
-    auto rot_lane = [&](double v, int64_t pos) -> double {
-      const double w = __shfl_xor(v, 1);
-      float c, sn;
-      rope_cos_sin(a.rope, pos, d >> 1, c, sn);
-      return (d & 1) ? w * (double)sn + v * (double)c : v * (double)c - w * (double)sn;
-    };
-#pragma unroll
-    for (int i = 0; i < kThinMaxQ; ++i) {
-      if (i >= a.n_q) continue;  // (not break: the loop stays unrolled, the arrays in registers)
-      raw_tot += (float)x[i];
-      if (ROPE) x[i] = rot_lane(x[i], past + i);
-      run += x[i];
-      const int sp = slot0 + i - (slot0 + i >= a.ring ? a.ring : 0);
-      col[(int64_t)sp * D] = run;
-      const int64_t t = past + i - a.n_local;
-      if (t >= a.n_init) {
-        double h = ht[i], k = kt[i];
-        if (t >= past) {
-          // token of this chunk: its running sum was written by this thread above
-          const int st = sp - a.n_local + (sp < a.n_local ? a.ring : 0);
-          h = col[(int64_t)st * D];
-          k = Elem<T>::load((const T*)a.k_src + (int64_t)bg * a.kv_head_stride + (t - past) * D + d);
-        }
-        // positional remap: the input key turned to its own position, unrounded
-        if (ROPE) k = rot_lane(k, t);
-        double part = k * (run - h);
-#pragma unroll
-        for (int o = 1; o < kRpartDims; o <<= 1) part += __shfl_xor(part, o);
-        if ((d % kRpartDims) == 0)
-          a.rpart[((int64_t)bg * (D / kRpartDims) + d / kRpartDims) * a.ring + (int)(t % a.ring)] = part;
-      }
-    }
-    if (qbar != nullptr) qbar[(int64_t)bg * D + d] = ROPE ? raw_tot : (float)(run - base);
+    thin_scan_block<T, GT, ROPE>(a, blk, qbar);
     return;
   }
 
@@ -548,6 +561,88 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
   }
 }
 
+// The append of a few tokens and unit scoring in one launch, for steps that build no
+// units (decoding, all but one step in l_bs).  Roles along the grid: [thin scan | copy
+// | score].  A scoring block needs nothing of the append: with so few tokens it sums
+// their queries itself (in float64, as the scan's total is), while its key sums are
+// on their way.  It takes 64 units, each unit's D dims split over its 8 waves (see
+// score_kernel).  One launch and one wait fewer per decoding step, and the scan's
+// latency hides behind the key sums.  Together with the selection inside the decode
+// kernel, two launches fewer: a step of one sequence at 32K 27.0 -> 22.5 us, of 16 at
+// 128K 128.6 -> 124.5, of 8 at 2K to 120K 73 -> 68.
+template <typename T, int GT, int D, bool ROPE>
+__global__ void __launch_bounds__(kThreads) append_score_kernel(AppendArgs a, ThinScoreArgs sc, int n_thin, int n_copy,
+                                                                int n_copy_per_head) {
+  int blk = blockIdx.x;
+  if (blk < n_thin) {
+    thin_scan_block<T, GT, ROPE>(a, blk, nullptr);
+    return;
+  }
+  blk -= n_thin;
+  if (blk < n_copy) {
+    copy_block<T, ROPE>(a, blk, n_copy_per_head);
+    return;
+  }
+  blk -= n_copy;
+  constexpr int NC = D / 4, CPW = NC / kWaves, kUnits = 64;
+  const int per_row = (sc.n_units + kUnits - 1) / kUnits;
+  const int bg = blk / per_row;
+  const int b = bg / a.n_kv_heads, g = bg - b * a.n_kv_heads;
+  int n_units = sc.n_units;
+  if (a.var.on) {
+    const int64_t evicted = a.var.past[b] - a.n_init - a.n_local;
+    n_units = evicted > 0 ? (int)(evicted / sc.block_size) : 0;
+  }
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int u = (blk - bg * per_row) * kUnits + lane;
+  const bool live = u < n_units;
+  // a thread past the last unit reads unit 0 (always present) and stores nothing
+  const float4* ks = (const float4*)sc.unit_ksum + (int64_t)bg * NC * sc.max_units + (live ? u : 0);
+  float4 k4[CPW];
+#pragma unroll
+  for (int c = 0; c < CPW; ++c) k4[c] = ks[(int64_t)(w * CPW + c) * sc.max_units];
+  __shared__ float qbar[D];
+  __shared__ float part[kWaves][kUnits];
+  const int G = GT > 0 ? GT : a.n_q_heads / a.n_kv_heads;
+  const int t = threadIdx.x;
+  if (t < D) {
+    const T* q = (const T*)a.q + (int64_t)(b * a.n_q_heads + g * G) * a.q_head_stride + t;
+    double x = 0.0;
+    for (int i = 0; i < a.n_q; ++i)
+      for (int h = 0; h < G; ++h) x += (double)Elem<T>::load(q + h * a.q_head_stride + (int64_t)i * D);
+    qbar[t] = (float)x;
+  }
+  __syncthreads();
+  if (ROPE) {  // the memory keys sit at distance l_L from every current token
+    float x0 = 0.f, x1 = 0.f;
+    if (t < D / 2) {
+      x0 = qbar[2 * t];
+      x1 = qbar[2 * t + 1];
+    }
+    __syncthreads();
+    if (t < D / 2) {
+      const float c = a.rope.mem_cos[t], sn = a.rope.mem_sin[t];
+      qbar[2 * t] = x0 * c - x1 * sn;
+      qbar[2 * t + 1] = x0 * sn + x1 * c;
+    }
+    __syncthreads();
+  }
+  float acc = 0.f;
+#pragma unroll
+  for (int c = 0; c < CPW; ++c) {
+    const int d = 4 * (w * CPW + c);
+    acc += qbar[d] * k4[c].x + qbar[d + 1] * k4[c].y + qbar[d + 2] * k4[c].z + qbar[d + 3] * k4[c].w;
+  }
+  part[w][lane] = acc;
+  __syncthreads();
+  if (w == 0 && live) {
+    float s = part[0][lane];
+#pragma unroll
+    for (int j = 1; j < kWaves; ++j) s += part[j][lane];
+    sc.scores[(int64_t)bg * sc.score_stride + u] = s;
+  }
+}
+
 }  // namespace
 
 template <int DT>
@@ -606,6 +701,48 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t s, float* qbar, const 
   if (fused_build != nullptr) ba = *fused_build;
   else std::memset(&ba, 0, sizeof(ba));
   return a.head_dim == 128 ? launch_append_d<128>(a, ba, g, s, qbar) : launch_append_d<64>(a, ba, g, s, qbar);
+}
+
+template <typename T, int GT, bool ROPE>
+static void launch_append_score_t(const AppendArgs& a, const ThinScoreArgs& sc, dim3 grid, int n_thin, int n_copy,
+                                  int per_head, hipStream_t s) {
+  if (a.head_dim == 128)
+    hipLaunchKernelGGL((append_score_kernel<T, GT, 128, ROPE>), grid, dim3(kThreads), 0, s, a, sc, n_thin, n_copy, per_head);
+  else
+    hipLaunchKernelGGL((append_score_kernel<T, GT, 64, ROPE>), grid, dim3(kThreads), 0, s, a, sc, n_thin, n_copy, per_head);
+}
+template <typename T, int GT>
+static void launch_append_score_r(const AppendArgs& a, const ThinScoreArgs& sc, dim3 grid, int n_thin, int n_copy,
+                                  int per_head, hipStream_t s) {
+  if (a.rope.on) launch_append_score_t<T, GT, true>(a, sc, grid, n_thin, n_copy, per_head, s);
+  else launch_append_score_t<T, GT, false>(a, sc, grid, n_thin, n_copy, per_head, s);
+}
+
+hipError_t launch_append_score(const AppendArgs& a, const ThinScoreArgs& sc, hipStream_t s) {
+  static_assert(kThinAppend == kThinMaxQ, "one thin scan");
+  if (a.n_q < 1 || a.n_q > kThinAppend) return hipErrorInvalidValue;
+  const int bh = a.batch * a.n_kv_heads;
+  const int n_thin = a.mean_repr ? 0 : (bh * a.head_dim + kThreads - 1) / kThreads;
+  int per_head = 0;
+  if (a.k_src != nullptr) {
+    const int vec_per_head = a.n_q * a.head_dim / (16 / (a.bf16 ? 2 : 4));
+    per_head = (vec_per_head + kThreads * kCopyPerThread - 1) / (kThreads * kCopyPerThread);
+  }
+  const int n_copy = per_head * bh, n_score = (sc.n_units + 63) / 64 * bh;
+  const dim3 grid(n_thin + n_copy + n_score);
+  const int G = a.n_q_heads / a.n_kv_heads;
+  if (a.bf16) {
+    switch (G) {
+      case 1: launch_append_score_r<bf16_t, 1>(a, sc, grid, n_thin, n_copy, per_head, s); break;
+      case 2: launch_append_score_r<bf16_t, 2>(a, sc, grid, n_thin, n_copy, per_head, s); break;
+      case 4: launch_append_score_r<bf16_t, 4>(a, sc, grid, n_thin, n_copy, per_head, s); break;
+      case 8: launch_append_score_r<bf16_t, 8>(a, sc, grid, n_thin, n_copy, per_head, s); break;
+      default: launch_append_score_r<bf16_t, 0>(a, sc, grid, n_thin, n_copy, per_head, s); break;
+    }
+  } else {
+    launch_append_score_r<float, 0>(a, sc, grid, n_thin, n_copy, per_head, s);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace infllm

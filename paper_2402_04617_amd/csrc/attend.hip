@@ -358,6 +358,12 @@ bool attend_uses_mfma(const AttendArgs& a) {
   return a.geom.n_q > 0 && a.bf16 && !decode_eligible(a.bf16, a.geom.n_q, G, a.geom.n_sel);
 }
 
+int attend_select_max(const AttendArgs& a) {
+  if (attend_uses_mfma(a)) return a.geom.idx_stride <= kFusedSelectMaxK ? kFusedSelectMax : -1;
+  const int G = a.n_q_heads / a.n_kv_heads;
+  return a.geom.n_q > 0 && decode_eligible(a.bf16, a.geom.n_q, G, a.geom.n_sel) ? kDecodeSelMax : -1;
+}
+
 hipError_t launch_attend(const AttendArgs& a, hipStream_t s) {
   if (a.geom.n_q == 0) return hipSuccess;
   const int G = a.n_q_heads / a.n_kv_heads;

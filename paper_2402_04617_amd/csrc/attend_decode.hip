@@ -19,6 +19,7 @@
 // through LDS into one partial result per workgroup, and the log-sum-exp merge
 // of Section 3.1's split key set joins the workgroups.
 #include "launch.h"
+#include "topk_select.h"
 
 namespace infllm {
 namespace {
@@ -81,6 +82,13 @@ __device__ __forceinline__ void bf16x8_to_f32(const uint4& raw, float (&f)[8]) {
   }
 }
 
+// 16 bytes of a K or V row, which no other workgroup reads: past the caches' reuse
+// (non-temporal; a 16 x 128K step 136 -> 130 us).
+__device__ __forceinline__ uint4 load_once(const char* p) {
+  const u32x4 w = __builtin_nontemporal_load((const u32x4*)p);
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
 // Byte offset in the (sequence, kv head) slice of the store of the row of
@@ -103,17 +111,21 @@ __device__ __forceinline__ uint32_t key_byte_offset(const StepGeom& g, const int
   return (uint32_t)(g.local_begin + (w - sel_len)) * row_bytes;
 }
 
-template <int D, int G>
+// NB: tile buffers.  3 (two tiles in flight while one is scored) for long runs of
+// keys; 4 where a wave has at most four tiles, so that no padding tile is loaded and
+// all but one tile's loads are issued at once (one sequence at 32K 13.6 -> 12.1 us;
+// 16 at 128K 105.5 -> 106, with more buffers slower still).
+template <int D, int G, int NB>
 __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(AttendArgs a) {
   constexpr int LPK = D / 8;      // lanes per key row
   constexpr int KPI = 64 / LPK;   // keys per wave-wide load
   constexpr int NI = 2;           // K (and V) loads per lane per tile
   constexpr int TK = KPI * NI;    // keys per tile
-  constexpr int NB = 3;           // tile buffers: two tiles in flight while one is scored
 
   __shared__ float cm[kDecodeWaves][G], cl[kDecodeWaves][G];
   __shared__ __attribute__((aligned(16))) float co[kDecodeWaves][G][D];
   __shared__ int32_t sidx[kDecodeMaxSel];
+  __shared__ tk::WaveSelSmem wsm;
   __shared__ float fo[G][D];  // this part's output rows before the fp16 write
 
   const int part = blockIdx.x % a.parts;
@@ -125,7 +137,19 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(Attend
   const int mem_len = sq.mem_len, parts_mem = sq.parts_mem;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane % LPK, r = lane / LPK;  // 16-byte piece of the row, key slot of the load
-  for (int j = tid; j < geo.n_sel; j += 64 * kDecodeWaves) sidx[j] = a.idx[(int64_t)bg * geo.idx_stride + j];
+  // Lookup: from idx, or (idx_out set: rows of at most kDecodeSelMax scores) selected
+  // here by the first wave of every workgroup -- a launch fewer before the keys can be
+  // read -- and written out by part 0.
+  const bool select = a.idx_out != nullptr;
+  const bool sel_all = geo.n_sel == 0 || geo.n_sel == geo.n_units;
+  uint32_t wkey[tk::kWavePer];
+  if (!select) {
+    for (int j = tid; j < geo.n_sel; j += 64 * kDecodeWaves) sidx[j] = a.idx[(int64_t)bg * geo.idx_stride + j];
+  } else if (!sel_all) {
+    if (wave == 0) tk::load_wave_keys(a.sel_scores + (int64_t)bg * a.sel_stride, geo.n_units, wkey);
+  } else {
+    for (int j = tid; j < geo.n_sel; j += 64 * kDecodeWaves) sidx[j] = j;
+  }
 
   // This wave's keys: the parts split the virtual axis evenly, in whole tiles per
   // wave.  With the positional remap parts [0, parts_mem) split the memory keys
@@ -179,7 +203,16 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(Attend
       }
     }
   }
+  if (select && !sel_all && wave == 0) {
+#pragma unroll
+    for (int j = 0; j < tk::kWavePer; ++j) wkey[j] = tk::order_key(__uint_as_float(wkey[j]));
+    tk::wave_select<tk::kWavePer>(wkey, geo.n_units, geo.n_sel, sidx, wsm);
+  }
   __syncthreads();
+  if (select && part == 0) {
+    int32_t* orow = a.idx_out + (int64_t)bg * geo.idx_stride;
+    for (int j = tid; j < geo.idx_stride; j += 64 * kDecodeWaves) orow[j] = j < geo.n_sel ? sidx[j] : -1;
+  }
 
   // uniform slice bases; per-lane 32-bit byte offsets (row offset + this lane's piece).
   // Local keys come rotated from k_rot under the remap.
@@ -196,8 +229,8 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(Attend
       const uint32_t o = v < vw1 ? key_byte_offset(geo, sidx, v, D * 2) : kNoKey;
       valid[buf][i] = o != kNoKey;
       const uint32_t oc = (o == kNoKey ? 0u : o) + piece;
-      kb[buf][i] = *(const uint4*)(kbase + oc);
-      vb[buf][i] = *(const uint4*)(vbase + oc);
+      kb[buf][i] = load_once(kbase + oc);
+      vb[buf][i] = load_once(vbase + oc);
     }
   };
 
@@ -362,13 +395,22 @@ template <int D>
 hipError_t launch_decode_d(const AttendArgs& a, hipStream_t s) {
   const int G = a.n_q_heads / a.n_kv_heads;
   const dim3 grid(a.parts * a.batch * a.n_kv_heads), block(64 * kDecodeWaves);
+  // tiles of a wave (2 loads of 64 / (D/8) keys each), as the kernel cuts them
+  const int tk_keys = 2 * 64 / (D / 8), waves = a.parts * kDecodeWaves;
+  const bool few = a.geom.n_virtual <= 4 * tk_keys * waves;
+#define INFLLM_DECODE(GG)                                                                                      \
+  do {                                                                                                         \
+    if (few) hipLaunchKernelGGL((attend_decode_kernel<D, GG, 4>), grid, block, 0, s, a);                        \
+    else hipLaunchKernelGGL((attend_decode_kernel<D, GG, 3>), grid, block, 0, s, a);                            \
+  } while (0)
   switch (G) {
-    case 1: hipLaunchKernelGGL((attend_decode_kernel<D, 1>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((attend_decode_kernel<D, 2>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((attend_decode_kernel<D, 4>), grid, block, 0, s, a); break;
-    case 8: hipLaunchKernelGGL((attend_decode_kernel<D, 8>), grid, block, 0, s, a); break;
+    case 1: INFLLM_DECODE(1); break;
+    case 2: INFLLM_DECODE(2); break;
+    case 4: INFLLM_DECODE(4); break;
+    case 8: INFLLM_DECODE(8); break;
     default: return hipErrorInvalidValue;
   }
+#undef INFLLM_DECODE
   return hipGetLastError();
 }
 

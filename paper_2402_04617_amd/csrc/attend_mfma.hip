@@ -93,7 +93,6 @@ struct Smem {
   uint32_t rows[kRowTable];  // store position of each key group of a window of tiles (kNoRow: skipped entry)
   int32_t sidx[kSelLds];    // the lookup row (its first kSelLds entries)
   uint8_t kvalid[NBUF][KB];
-  int sel_ok;
 };
 
 // Publish LDS tiles to the workgroup: wait until at most N of this wave's
@@ -113,9 +112,9 @@ __device__ __forceinline__ void publish_barrier() {
   lds_barrier();
 }
 
-// SEL > 0: the workgroups select the lookup themselves from a.sel_scores, SEL
-// keys of a score row per thread (2: rows of at most kFusedSelectShort units;
-// 16: longer rows, filtered first) -- kernels of their own, so that the plain
+// SEL > 0: the workgroups select the lookup themselves from a.sel_scores (2: rows of
+// at most kFusedSelectShort units, by one wave; 16: longer rows, 16 keys per thread
+// of all waves) -- kernels of their own, so that the plain
 // kernel's code is unaffected.  MASS (with SEL):
 // for every tile of the looked-up units the kernel also stores, per query row,
 // the tile's sum of P = exp2(S*c2 - m) and the running max m it was formed
@@ -243,23 +242,22 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   // Lookup inside the attention: such a workgroup selects the units itself; the
   // workgroup of row tile 0 and part 0 always does, and writes the row out (also
   // without units: it is then all -1).  Every entry is valid.
-  static_assert(SEL == 0 || SEL == 2 || SEL == tk::kMaxPer, "select keys per thread");
-  static_assert(tk::kThreads == 64 * NWAVE && 2 * tk::kThreads >= kFusedSelectShort &&
-                    tk::kMaxPer * tk::kThreads >= kFusedSelectMax,
-                "select layout");
+  static_assert(SEL == 0 || SEL == 2 || SEL == tk::kMaxPer, "select variants");
+  static_assert(tk::kThreads == 64 * NWAVE && tk::kMaxPer * tk::kThreads >= kFusedSelectMax, "select layout");
   const bool sel_writer = SEL > 0 && rt == 0 && part == 0;
   const bool sel_here = SEL > 0 && (sel_writer || units_here);
   const bool sel_all = geo.n_sel == 0 || geo.n_sel == geo.n_units;  // every unit (or none) is looked up
-  const bool sel_waves = geo.n_sel <= tk::kWaveK;                   // by the single-wave select
+  const bool sel_waves = SEL == 2 || geo.n_sel <= tk::kWaveK;       // by single waves
   const float* srow = SEL > 0 ? a.sel_scores + (int64_t)bg * a.sel_stride : nullptr;
   // scores of the single-wave select: short rows in the first wave, 16 per lane; long
   // rows 16 per lane of every wave (loaded before the queries, whose latency overlaps)
-  constexpr int WPER = 16;
+  constexpr int WPER = tk::kWavePer;
+  static_assert(tk::kWaveRow >= kFusedSelectShort, "a short row fits one wave");
   uint32_t wkey[WPER] = {};
   if (SEL > 0 && sel_here && !sel_all && sel_waves && (SEL > 2 || wave == 0)) {
 #pragma unroll
     for (int j = 0; j < WPER; ++j)
-      wkey[j] = __float_as_uint(srow[min(wave * 64 * WPER + 64 * j + lane, geo.n_units - 1)]);
+      wkey[j] = __float_as_uint(srow[min(wave * tk::kWaveRow + 64 * j + lane, geo.n_units - 1)]);
   }
 
   // The wave's query rows go to LDS first, whole rows at a time, into the V buffers
@@ -338,20 +336,16 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
       if constexpr (SEL > 2) {
         done = tk::long_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::LongSelSmem*)sm.rows);
       } else {
-        if (wave == 0) {
-          const bool ok = tk::wave_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx,
-                                               *(tk::WaveSelSmem*)sm.rows);
-          if (lane == 0) sm.sel_ok = ok;
-        }
-        lds_barrier();
-        done = sm.sel_ok != 0;
+        if (wave == 0)
+          tk::wave_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::WaveSelSmem*)sm.rows);
+        done = true;
       }
     }
-    if (!done) {
-      // more units than the wave select takes, or too many ties: the radix select,
-      // SEL keys per thread (long rows filtered first; the filter declines, uniformly,
-      // when the bound it finds leaves more than a thread's worth of candidates)
-      constexpr int SK = SEL > 0 ? SEL : 1;
+    if constexpr (SEL > 2) if (!done) {
+      // more units than the waves' select takes, or too many ties: the radix select,
+      // SEL keys per thread, filtered first (the filter declines, uniformly, when the
+      // bound it finds leaves more than a thread's worth of candidates)
+      constexpr int SK = SEL;
       uint32_t skey[SK];
 #pragma unroll
       for (int j = 0; j < SK; ++j) skey[j] = tk::order_key(srow[min(tid + j * tk::kThreads, geo.n_units - 1)]);
@@ -360,7 +354,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
       uint32_t thr;
       int rem;
       bool ge;
-      if constexpr (SEL > 2) done = geo.n_sel <= tk::kThreads && tk::filtered_select<SK>(skey, geo.n_units, geo.n_sel, sm.sidx);
+      done = geo.n_sel <= tk::kThreads && tk::filtered_select<SK>(skey, geo.n_units, geo.n_sel, sm.sidx);
       if (!done) {
         tk::radix_threshold<SK>(skey, valid, geo.n_sel, thr, rem, ge);
         tk::write_selection<SK>(skey, valid, index, thr, rem, ge, geo.n_sel, sm.sidx);

@@ -129,12 +129,15 @@ hipError_t launch_select_topk_var(int rows, const float* scores, int stride, int
 constexpr int kMfmaWaves = 8;
 constexpr int kMfmaTargetWgs = 256;
 // Workgroups the bf16 decode kernel aims for (two per compute unit), and the
-// fewest keys it gives one workgroup.
+// fewest keys it gives one workgroup (one sequence at 32K, 6,265 keys: 25 parts of
+// 256 keys 14.9 us, 50 of 128 13.5; the merge takes either in 4.3).
 constexpr int kDecodeTargetWgs = 512;
-constexpr int kDecodeMinKeysPerWg = 256;
+constexpr int kDecodeMinKeysPerWg = 128;
 // Most selected units the decode kernel stages in LDS; longer lookups decode on
 // the matrix-core kernel.
 constexpr int kDecodeMaxSel = 1024;
+// Longest score row the decode kernel selects from itself (one wave).
+constexpr int kDecodeSelMax = 1024;
 
 // Score rows the matrix-core attention selects from itself: rows of at most
 // kFusedSelectShort units hold two keys per thread, longer rows up to
@@ -168,7 +171,8 @@ struct AttendArgs {
   int n_local;
   const int32_t* idx;
   // Lookup inside the attention (idx_out non-null; matrix-core kernel,
-  // n_units <= kFusedSelectMax, n_sel <= kFusedSelectMaxK): a workgroup whose tiles hold unit
+  // n_units <= kFusedSelectMax, n_sel <= kFusedSelectMaxK; decode kernel, n_units <=
+  // kDecodeSelMax): a workgroup whose tiles hold unit
   // keys selects its kv head's n_sel units from the score row itself, with the
   // select of infllm_select_topk, instead of reading idx; the workgroup of row
   // tile 0 and part 0 also writes the row to idx_out (the -1 padding included).
@@ -197,6 +201,17 @@ struct AttendArgs {
   FastDiv d_row_tiles, d_parts, d_kv, d_group, d_block;
   bool bf16;
 };
+struct ThinScoreArgs {
+  const float* unit_ksum;
+  float* scores;
+  int max_units, n_units, block_size;  // n_units: the largest of the batch
+  int64_t score_stride;
+};
+// The append of a few tokens (at most kThinAppend, no units to build) and the scores
+// of all units against them in one launch: a.rope must hold both tables.
+constexpr int kThinAppend = 8;
+hipError_t launch_append_score(const AppendArgs& a, const ThinScoreArgs& sc, hipStream_t s);
+
 // The step of sequence b as a kernel sees it.
 struct SeqStep {
   StepGeom geom;
@@ -221,6 +236,9 @@ __host__ __device__ inline SeqStep seq_step(const AttendArgs& a, int b) {
 int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int n_q, int n_sel, int n_virtual,
                         int max_parts, int* row_waves);
 hipError_t launch_attend(const AttendArgs& a, hipStream_t s);
+// Most scores a row may hold for the launch to select its units itself (see
+// AttendArgs::idx_out); -1 where its kernel never does.
+int attend_select_max(const AttendArgs& a);
 // Whether launch_attend runs the matrix-core kernel for these arguments.
 bool attend_uses_mfma(const AttendArgs& a);
 

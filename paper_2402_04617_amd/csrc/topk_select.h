@@ -344,7 +344,7 @@ __device__ bool filtered_select(const uint32_t (&key)[PER], int n, int k_eff, in
 }
 
 // ---- selection by single waves ----------------------------------------------
-// For k_eff <= kWaveK.  A wave holds up to 64*PER keys, PER per lane; the k-th
+// A wave holds up to 64*PER keys, PER per lane; the k-th
 // largest of the 64 lane maxima (lanes without a key hold 0) is a bound with at
 // least k keys at or above it, found bit by bit with ballots.  The few keys at or
 // above the bound (about 1.4 k for random scores) are compacted in index order and
@@ -445,24 +445,63 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+// One wave, any k_eff < n: the k_eff-th largest key bit by bit over all keys, then the
+// keys above it and the first equal ones, in index order.
+template <int PER>
+__device__ __forceinline__ void wave_select_exact(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out) {
+  const int l = threadIdx.x & 63;
+  uint32_t T = 0;
+  for (int s = 31; s >= 0; --s) {
+    const uint32_t t = T | (1u << s);
+    int c = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) c += __popcll(__ballot(l + 64 * j < n && key[j] >= t));
+    T = c >= k_eff ? t : T;
+  }
+  int equal = k_eff;  // keys equal to T to keep
+#pragma unroll
+  for (int j = 0; j < PER; ++j) equal -= __popcll(__ballot(l + 64 * j < n && key[j] > T));
+  int base = 0, seen = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const bool live = l + 64 * j < n, eq = live && key[j] == T;
+    const unsigned long long me = __ballot(eq);
+    const bool keep = (live && key[j] > T) || (eq && seen + lanes_below(me) < equal);
+    const unsigned long long mk = __ballot(keep);
+    if (keep) out[base + lanes_below(mk)] = l + 64 * j;
+    base += __popcll(mk);
+    seen += __popcll(me);
+  }
+}
+
 // One wave: the k_eff largest of n <= 64*PER keys (lane l: element l + 64*j),
-// 0 < k_eff <= kWaveK, k_eff < n.  False (wave-uniform) when too many keys tie at
-// the bound; nothing is written then.
+// 0 < k_eff < n.
 typedef Candidates<kWaveCand> WaveSelSmem;
 template <int PER>
-__device__ __forceinline__ bool wave_select(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out,
+__device__ __forceinline__ void wave_select(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out,
                                             WaveSelSmem& sm) {
   const int l = threadIdx.x & 63;
-  auto valid = [&](int j) { return l + 64 * j < n; };
-  const uint32_t T = lane_bound(lane_max<PER>(key, valid), k_eff);
+  if (k_eff <= kWaveK) {
+    auto valid = [&](int j) { return l + 64 * j < n; };
+    const uint32_t T = lane_bound(lane_max<PER>(key, valid), k_eff);
 #pragma unroll
-  for (int j = 0; j < kWaveCand; j += 64) sm.key[j + l] = 0u;
-  wave_lds_fence();
-  const int n_cand = compact_candidates<PER>(key, valid, [&](int j) { return l + 64 * j; }, T, 0, sm);
-  if (n_cand > kWaveCand) return false;
-  wave_lds_fence();
-  rank_candidates(sm, n_cand, k_eff, out);
-  return true;
+    for (int j = 0; j < kWaveCand; j += 64) sm.key[j + l] = 0u;
+    wave_lds_fence();
+    const int n_cand = compact_candidates<PER>(key, valid, [&](int j) { return l + 64 * j; }, T, 0, sm);
+    wave_lds_fence();
+    if (n_cand <= kWaveCand) {
+      rank_candidates(sm, n_cand, k_eff, out);
+      return;
+    }
+  }
+  wave_select_exact<PER>(key, n, k_eff, out);  // many units, or too many ties at the bound
+}
+constexpr int kWavePer = 16;                 // keys per lane of the single-wave select
+constexpr int kWaveRow = 64 * kWavePer;      // longest row it takes
+// Lane l's key of element l + 64*j of a row of n scores (clamped past the end).
+__device__ __forceinline__ void load_wave_keys(const float* __restrict__ s, int n, uint32_t (&key)[kWavePer]) {
+#pragma unroll
+  for (int j = 0; j < kWavePer; ++j) key[j] = __float_as_uint(s[min(64 * j + (int)(threadIdx.x & 63), n - 1)]);
 }
 
 // The whole workgroup (kThreads): rows of up to kThreads*kMaxPer keys, wave w
