@@ -10,7 +10,7 @@
 // finished by a DPP all-reduce over the lanes of a key, so every lane of the key
 // holds its score and reuses it as the weight of the same key's value piece.
 //
-// The virtual key axis of each (sequence, kv head) is split evenly into `parts`
+// The virtual key axis of each (sequence, kv head) is split by cost into `parts`
 // workgroups (the host picks enough parts to give every compute unit two
 // workgroups), and each workgroup's keys evenly over its 4 waves, in whole
 // tiles.  Each wave runs an online softmax over its keys, two tiles of loads
@@ -151,7 +151,7 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(Attend
     for (int j = tid; j < geo.n_sel; j += 64 * kDecodeWaves) sidx[j] = j;
   }
 
-  // This wave's keys: the parts split the virtual axis evenly, in whole tiles per
+  // This wave's keys: the parts split the virtual axis by cost, in whole tiles per
   // wave.  With the positional remap parts [0, parts_mem) split the memory keys
   // [0, mem_len) (I and the units) and the other parts the local keys.
   const bool remap = a.rope.on != 0;
@@ -165,10 +165,32 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(Attend
     rpart = part - parts_mem;
     rparts = a.parts - parts_mem;
   }
-  const int n_waves_total = rparts * kDecodeWaves;
-  const int kpw = ((rv1 - rv0 + n_waves_total - 1) / n_waves_total + TK - 1) / TK * TK;
-  const int vw0 = rv0 + (rpart * kDecodeWaves + wave) * kpw;
-  const int vw1 = min(vw0 + kpw, rv1);
+  int vw0, vw1;
+  if (NB == 4 || parts_mem > 0) {
+    const int n_waves_total = rparts * kDecodeWaves;
+    const int kpw = ((rv1 - rv0 + n_waves_total - 1) / n_waves_total + TK - 1) / TK * TK;
+    vw0 = rv0 + (rpart * kDecodeWaves + wave) * kpw;
+    vw1 = min(vw0 + kpw, rv1);
+  } else {
+    // Long runs: a key of I or of a unit (32 KB pieces all over the store, and the
+    // lookup to wait for) is charged kMemKey local ones, so that the parts end
+    // together (16 at 128K: parts of equal key counts ended 104, 106, 95 and 96 us in
+    // on average, the step took 123.4 us; 118.7 now, 119.7 at 1.15).
+    constexpr float kMemKey = 1.1f;
+    constexpr int kStep = TK * kDecodeWaves;
+    const float c_mem = kMemKey * (float)mem_len;
+    const float c_part = (c_mem + (float)(rv1 - mem_len)) * __builtin_amdgcn_rcpf((float)rparts);
+    auto bound = [&](int pp) -> int {
+      if (pp == rparts) return rv1;
+      const float c = c_part * (float)pp;
+      const float v = c <= c_mem ? c * (1.f / kMemKey) : (float)mem_len + (c - c_mem);
+      return min(((int)v + kStep / 2) / kStep * kStep, rv1);
+    };
+    const int pv0 = bound(rpart), pv1 = bound(rpart + 1);
+    const int kpw = ((pv1 - pv0 + kDecodeWaves - 1) / kDecodeWaves + TK - 1) / TK * TK;
+    vw0 = min(pv0 + wave * kpw, pv1);
+    vw1 = min(vw0 + kpw, pv1);
+  }
   const int nt = vw1 > vw0 ? (vw1 - vw0 + TK - 1) / TK : 0;
 
   // Query rows of the group: this lane's 8 dims as 4 bf16 pairs; the dot products
