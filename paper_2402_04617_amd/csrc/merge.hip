@@ -4,11 +4,11 @@
 //
 // One thread per (row, 16 bytes of partial row): 8 dims of a scaled-fp16 partial
 // (bfloat16 inputs; value * 2^exp[row] restores the row) or 4 dims of a float32
-// one.  Up to 8 parts: one thread takes them all (CH = the part count, or 8), every
-// load issued before the first use.  More parts (decoding): a workgroup per row, its
-// threads split into groups that take every GR-th part and are joined in LDS -- with
-// few rows the parts are the only parallelism (25 parts of 32 rows, one thread per
-// piece and 8 parts at a time: 6.8 us; split: 4.3).
+// one.  A thread takes all parts, CH at a time (CH = the part count, or 8), every load
+// of those issued before the first use.  More than 8 parts of few rows (decoding): a
+// workgroup per row, its threads split into groups that take every GR-th part and are
+// joined in LDS -- the parts are then the only parallelism (25 parts of 32 rows: 6.8 us
+// one thread per piece, 4.3 split; 16 parts of 2,048 rows: 3.7 and 6.5).
 #include "launch.h"
 
 namespace infllm {
@@ -35,24 +35,42 @@ __device__ __forceinline__ void load_piece(const MergeArgs& a, int64_t pr, int c
     o[3] = w.w;
   }
 }
-// The softmax join of CH parts: running maximum, weight sum and weighted rows.
-template <int CH, int DPT>
-__device__ __forceinline__ void join(const float (&l)[CH], const float (&o)[CH][DPT], int n, float& M, float& tot,
-                                     float (&acc)[DPT]) {
+// Joins parts first, first + step, ... (every load of CH of them issued before the
+// first use) into a running maximum, weight sum and weighted row.  ONCE: there are at
+// most CH of them.
+template <bool HALF, int CH, bool ONCE>
+__device__ __forceinline__ void join_parts(const MergeArgs& a, int row, int c, int first, int step, float& M, float& tot,
+                                           float (&acc)[HALF ? 8 : 4]) {
+  constexpr int DPT = HALF ? 8 : 4;
   M = -__builtin_inff();
-#pragma unroll
-  for (int j = 0; j < CH; ++j)
-    if (j < n) M = fmaxf(M, l[j]);
   tot = 0.f;
 #pragma unroll
   for (int e = 0; e < DPT; ++e) acc[e] = 0.f;
-  if (M == -__builtin_inff()) return;  // nothing visible
+  for (int p0 = first; p0 < a.parts; p0 += CH * step) {
+    float l[CH], o[CH][DPT];
 #pragma unroll
-  for (int j = 0; j < CH; ++j) {
-    const float w = (j < n && l[j] != -__builtin_inff()) ? expf(l[j] - M) : 0.f;
-    tot += w;
+    for (int j = 0; j < CH; ++j)
+      load_piece<HALF>(a, (int64_t)min(p0 + j * step, a.parts - 1) * a.rows + row, c, o[j], l[j]);
+    float m_new = M;
 #pragma unroll
-    for (int e = 0; e < DPT; ++e) acc[e] += w * o[j][e];
+    for (int j = 0; j < CH; ++j)
+      if (p0 + j * step < a.parts) m_new = fmaxf(m_new, l[j]);
+    if (m_new == -__builtin_inff()) continue;  // nothing visible yet
+    if constexpr (!ONCE) {
+      const float r = M == -__builtin_inff() ? 0.f : expf(M - m_new);
+      tot *= r;
+#pragma unroll
+      for (int e = 0; e < DPT; ++e) acc[e] *= r;
+    }
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const float w = (p0 + j * step < a.parts && l[j] != -__builtin_inff()) ? expf(l[j] - m_new) : 0.f;
+      tot += w;
+#pragma unroll
+      for (int e = 0; e < DPT; ++e) acc[e] += w * o[j][e];
+    }
+    M = m_new;
+    if (ONCE) break;
   }
 }
 template <typename T, int DPT>
@@ -86,10 +104,8 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
   const int row = wg * rows_per_wg + threadIdx.x / tpr;
   const int c = threadIdx.x % tpr;
   if (row >= a.rows) return;
-  float l[CH], o[CH][DPT], M, tot, acc[DPT];
-#pragma unroll
-  for (int j = 0; j < CH; ++j) load_piece<HALF>(a, (int64_t)min(j, a.parts - 1) * a.rows + row, c, o[j], l[j]);
-  join<CH, DPT>(l, o, a.parts, M, tot, acc);
+  float M, tot, acc[DPT];
+  join_parts<HALF, CH, (CH < 8)>(a, row, c, 0, 1, M, tot, acc);
   store_piece<T, DPT>(a, row, c, M, tot, acc);
 }
 
@@ -101,24 +117,9 @@ __global__ void __launch_bounds__(256) merge_many_kernel(MergeArgs a) {
   const int tpr = a.head_dim / DPT, groups = 256 / tpr;  // 8 to 32 groups
   const int c = threadIdx.x % tpr, grp = threadIdx.x / tpr;
   __shared__ float sM[32], sT[32], sO[256 * DPT];
-  float M = -__builtin_inff(), tot = 0.f, acc[DPT];
-#pragma unroll
-  for (int e = 0; e < DPT; ++e) acc[e] = 0.f;
-  for (int p0 = grp; p0 < a.parts; p0 += CH * groups) {
-    float l[CH], o[CH][DPT], m, t, x[DPT];
-    const int n = (a.parts - p0 + groups - 1) / groups;  // parts left to this group
-#pragma unroll
-    for (int j = 0; j < CH; ++j)
-      load_piece<HALF>(a, (int64_t)min(p0 + j * groups, a.parts - 1) * a.rows + row, c, o[j], l[j]);
-    join<CH, DPT>(l, o, n, m, t, x);
-    const float mn = fmaxf(M, m);
-    if (mn == -__builtin_inff()) continue;
-    const float w0 = M == -__builtin_inff() ? 0.f : expf(M - mn), w1 = m == -__builtin_inff() ? 0.f : expf(m - mn);
-    tot = tot * w0 + t * w1;
-#pragma unroll
-    for (int e = 0; e < DPT; ++e) acc[e] = acc[e] * w0 + x[e] * w1;
-    M = mn;
-  }
+  float M, tot, acc[DPT];
+  if (a.parts <= CH * groups) join_parts<HALF, CH, true>(a, row, c, grp, groups, M, tot, acc);
+  else join_parts<HALF, CH, false>(a, row, c, grp, groups, M, tot, acc);
   if (c == 0) {
     sM[grp] = M;
     sT[grp] = tot;
@@ -142,12 +143,14 @@ __global__ void __launch_bounds__(256) merge_many_kernel(MergeArgs a) {
   store_piece<T, DPT>(a, row, c, M, tot, acc);
 }
 
+constexpr int kManyRows = 1024;  // most rows whose many parts are split over threads
+
 template <typename T, bool HALF>
 hipError_t launch_merge_t(const MergeArgs& a, hipStream_t s) {
   constexpr int DPT = HALF ? 8 : 4;
   const int rows_per_wg = 256 / (a.head_dim / DPT);
   const dim3 grid((a.rows + rows_per_wg - 1) / rows_per_wg), block(256);
-  if (a.parts > 8) {
+  if (a.parts > 8 && a.rows <= kManyRows) {
     hipLaunchKernelGGL((merge_many_kernel<T, HALF>), dim3(a.rows), block, 0, s, a);
     return hipGetLastError();
   }
