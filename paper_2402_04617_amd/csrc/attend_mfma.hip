@@ -99,13 +99,6 @@ struct Smem {
 // direct loads are still in flight (older loads -- the tiles about to be read
 // -- have landed in LDS) and its own LDS traffic is done, then barrier.  Written
 // out so that no wait for the younger loads is implied.
-__device__ __forceinline__ void lds_barrier() {
-  // LDS-only fences: order this wave's LDS accesses around the barrier without
-  // a wait for its outstanding global loads.
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 template <int N>
 __device__ __forceinline__ void publish_barrier() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N));

@@ -1,0 +1,45 @@
+"""Appends of several scan tiles (512 positions each) at once (GPU): the running query sums and the partial
+representative scores against float64 sums on the host, where tiles are full, ragged, of one position, and
+where the tokens that leave the window precede the chunk or lie inside it."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2402_04617_amd import infllm as F
+from tests.gpu_util import Layer, dev, host, log
+from tests.test_gpu_kernels import rand_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,G,D,lL,chunks", [
+    ("bf16", 4, 128, 1100, (700, 1536, 512)),  # tiles of all kinds: before the chunk, inside it
+    ("bf16", 3, 64, 2000, (1300, 1025)),       # run-time group size, a last tile of one position
+    ("f32", 2, 64, 40, (1100, 9, 600)),        # a window shorter than a tile
+    ("bf16", 8, 128, 513, (513, 1024, 1)),
+])
+def test_append_tiles(dtype, G, D, lL, chunks):
+    rng = np.random.default_rng(lL)
+    Hkv, B, lI, S = 2, 1, 5, sum(chunks)
+    ring = lL + max(chunks) + 7
+    p = F.params(G * Hkv, Hkv, D, lI, lL, 64, 2, 2, dtype)
+    q, k, v = rand_inputs(rng, G * Hkv, Hkv, S, D, dtype, B=B)
+    L = Layer(p, B, S, chunk=max(chunks), ring=ring)
+    qd, kd, vd = dev(q, dtype), dev(k, dtype), dev(v, dtype)
+    pref = np.cumsum(q.astype(np.float64).reshape(B, Hkv, G, S, D).sum(axis=2), axis=2)
+    past = 0
+    for n in chunks:
+        log(f"[append tiles] {dtype} G={G} D={D} l_L={lL} past={past} n={n}")
+        off = past * D * L.esize
+        F.infllm_append(p, L.mem.struct, qd.data_ptr() + off, S * D, kd.data_ptr() + off, vd.data_ptr() + off, S * D,
+                        n, past)
+        torch.cuda.synchronize()
+        got, part = host(L.mem.qprefix), host(L.mem.rpart)
+        for t in range(past, past + n):
+            assert np.allclose(got[:, :, t % ring], pref[:, :, t], rtol=1e-12, atol=1e-12), t
+        for pos in range(max(past, lI + lL), past + n):
+            t = pos - lL
+            w = k[:, :, t].astype(np.float64) * (pref[:, :, pos] - pref[:, :, t])
+            exp = w.reshape(B, Hkv, D // 8, 8).sum(-1)
+            assert np.allclose(part[:, :, :, t % ring], exp, rtol=1e-10, atol=1e-10), t
+        past += n
