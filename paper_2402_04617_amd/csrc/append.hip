@@ -41,6 +41,11 @@ constexpr int kThreads = 512;                  // threads of every block of the 
 constexpr int kWaves = kThreads / 64;
 constexpr int kSeg = 2;                        // positions per thread per tile: a 512-position chunk is one tile
 constexpr int kTile = (kThreads / 2) * kSeg;   // positions per scan tile
+// Chunks this short fit one wave's 32 segments: each wave of a scan block then takes a
+// slice of its own (with a block per slice, four sequences of 24 tokens took 512 mostly
+// idle blocks in rounds: 57.1 us per step, 51.8 with 64; one thread per dim, as for at
+// most kThinMaxQ positions: 70.6).
+constexpr int kWaveTile = 32 * kSeg;
 constexpr int kCopyPerThread = 4;              // 16-byte vectors per thread in copy blocks
 constexpr int kThinMaxQ = 8;                   // chunks this short take the one-thread-per-dim scan
 constexpr int kDPT = kRpartDims / 2;           // dimensions per scan thread (a slice's two halves)
@@ -155,6 +160,7 @@ struct AppendGrid {
   int n_qsum;           // query-sum blocks (Mean Repr: parts * batch * Hkv), 0 otherwise
   int qsum_parts;
   int n_scan;           // scan blocks
+  bool wave_slices;     // a scan block holds kWaves slices, one per wave (chunks of at most kWaveTile)
   bool thin;            // scan blocks are thin (one thread per (sequence*kv head, dim))
   int n_copy_per_head;  // copy blocks per (sequence, kv head)
 };
@@ -320,14 +326,17 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
   // HBM once instead of once per slice.
   const int slices = D / kRpartDims;
   if (grid.n_scan % kNumXcd == 0) blk = xcd_logical_block(blk, grid.n_scan);
-  const int bg = blk / slices;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool own = grid.wave_slices;  // this wave has a slice of its own
+  const int unit = own ? blk * kWaves + wave : blk;
+  if (unit >= a.batch * a.n_kv_heads * slices) return;  // whole waves
+  const int bg = unit / slices;
   const int b = bg / a.n_kv_heads, g = bg - b * a.n_kv_heads;
   const int64_t past = seq_past(a, b);
   // lanes [0, 32) of a wave take the slice's first kDPT dims, lanes [32, 64) the
   // other kDPT, for the same 32 position segments (a segment scan is a 32-lane scan)
-  const int half = (threadIdx.x >> 5) & 1, seg = (threadIdx.x >> 6) * 32 + (threadIdx.x & 31);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int slice = blk - bg * slices;
+  const int half = (threadIdx.x >> 5) & 1, seg = (own ? 0 : wave * 32) + (threadIdx.x & 31);
+  const int slice = unit - bg * slices;
   const int d0 = slice * kRpartDims + half * kDPT;
   const int G = GT > 0 ? GT : a.n_q_heads / a.n_kv_heads;
   const T* qb = (const T*)a.q + (int64_t)(b * a.n_q_heads + g * G) * a.q_head_stride + d0;
@@ -461,8 +470,8 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
 #pragma unroll
       for (int e = 0; e < kDPT; ++e) {
         const double y = wave_tot[w][half][e];
-        off[e] += (w < wave) ? y : 0.0;
-        tile_tot[e] += y;
+        off[e] += (!own && w < wave) ? y : 0.0;
+        tile_tot[e] += (!own || w == wave) ? y : 0.0;
       }
     }
     double part[kSeg];
@@ -563,7 +572,7 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
       for (int e = 0; e < kDPT; ++e) {
         float t = 0.f;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) t += wave_raw[w][half][e];
+        for (int w = 0; w < kWaves; ++w) t += (!own || w == wave) ? wave_raw[w][half][e] : 0.f;
         qbar[(int64_t)bg * D + d0 + e] = t;
       }
     }
@@ -701,9 +710,12 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t s, float* qbar, const 
   // query-sum blocks when scoring follows (qbar given).
   g.qsum_parts = score_qbar_parts(a.n_q_heads / a.n_kv_heads, a.n_q);
   g.n_qsum = (a.mean_repr && qbar != nullptr && a.n_q > 0) ? g.qsum_parts * a.batch * a.n_kv_heads : 0;
+  const int n_slices = a.batch * a.n_kv_heads * (a.head_dim / kRpartDims);
+  g.wave_slices = a.n_q <= kWaveTile;
   g.n_scan = (a.n_q <= 0 || a.mean_repr) ? 0
              : g.thin ? (a.batch * a.n_kv_heads * a.head_dim + kThreads - 1) / kThreads
-                      : a.batch * a.n_kv_heads * (a.head_dim / kRpartDims);
+             : g.wave_slices ? (n_slices + kWaves - 1) / kWaves
+                             : n_slices;
   g.n_copy_per_head = 0;
   if (a.k_src != nullptr && a.n_q > 0) {
     const int vec_per_head = a.n_q * a.head_dim / (16 / esize);

@@ -1,6 +1,6 @@
 """Appends of several scan tiles (512 positions each) at once (GPU): the running query sums and the partial
-representative scores against float64 sums on the host, where tiles are full, ragged, of one position, and
-where the tokens that leave the window precede the chunk or lie inside it."""
+representative scores against float64 sums on the host, where tiles are full, ragged, of one position, the
+chunk is short, and where the tokens that leave the window precede the chunk or lie inside it."""
 import numpy as np
 import pytest
 import torch
@@ -17,6 +17,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", 3, 64, 2000, (1300, 1025)),       # run-time group size, a last tile of one position
     ("f32", 2, 64, 40, (1100, 9, 600)),        # a window shorter than a tile
     ("bf16", 8, 128, 513, (513, 1024, 1)),
+    # short chunks: one thread per dim, 8 or 16 positions at a time; the window inside the chunk
+    ("bf16", 4, 128, 60, (100, 9, 16, 17, 32, 33, 8, 24)),
+    ("bf16", 3, 64, 12, (32, 31, 25)),
+    ("f32", 1, 128, 200, (230, 32, 1, 20)),
 ])
 def test_append_tiles(dtype, G, D, lL, chunks):
     rng = np.random.default_rng(lL)
