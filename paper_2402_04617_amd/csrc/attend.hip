@@ -31,8 +31,8 @@ constexpr int kF32Sel = 2048;  // lookup entries kept in LDS
 // 32 through two LDS buffers, loaded directly one tile ahead.
 //  S^T = K Q^T: A = K rows from LDS, B = the wave's Q rows in registers.  The
 //    contraction may take the dims in any order: a lane's half of k-steps 4i..4i+3
-//    is dims 8i + 4*gsel .. +4, so that one 16-byte read feeds four k-steps.  Even
-//    and odd k-steps go to two accumulators (a shorter chain, and a smaller error).
+//    is dims 8i + 4*gsel .. +4, so that one 16-byte read feeds four k-steps.
+//    Sums of 16 products are joined by additions (see scores).
 //  O^T += V^T P^T: B = the probabilities as S^T leaves them (k-step (a, b) pairs
 //    keys 8a + b and 8a + 4 + b, one per lane half), A = V rows from LDS; output
 //    block db holds dims DBLK*m + db, so that one read feeds all DBLK blocks.
@@ -41,7 +41,8 @@ constexpr int kF32Sel = 2048;  // lookup entries kept in LDS
 // instruction); with one wave per SIMD the softmax (expf, 16 scores per lane and
 // tile) is exposed.  With one vector-ALU dot product and a shuffle reduction per
 // (row, key) instead, a step of 256 queries of 8 heads (D 64) over 2,400 keys took
-// 228 us against 41 now, with an error against 64 bits of 5.7e-7 against 5.2e-7.
+// 228 us against 43 now (D 128 287 and 63, remapped 290 and 75), with an error against
+// 64 bits of 5.4 to 6.3e-7 against 4.3 to 4.4e-7 (three seeds).
 // With the positional remap (ROPE) a wave holds both forms of its query rows; a tile
 // of memory keys takes the one at distance l_L, a tile of local keys the other, and
 // the tile that holds both kinds takes both and picks per key.
@@ -166,16 +167,25 @@ __global__ void __launch_bounds__(64 * NW, 1) attend_f32_kernel(AttendArgs a) {
 
   // S^T of the tile in buffer `kt` against one form of the query rows
   auto scores = [&](const float* kt, const float* qx) {
-    f32x16 s0 = {}, s1 = {};
+    // Sums of 16 products, joined: chains of 32 (64 at D = 128) took 41 us where this
+    // takes 43, but left rows of short parts further from 64 bits than the vector ALU's
+    // sums had (40 queries of 2 heads: 5.1e-7, 4.3e-7 now, 4.5e-7 there).
+    f32x16 sum;
 #pragma unroll
-    for (int i = 0; i < QL / 4; ++i) {
-      const f32x4 kf = *(const f32x4*)(kt + n * D + 4 * ((2 * i + gsel) ^ (n & 15)));
-      s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[0], qx[4 * i], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[1], qx[4 * i + 1], s1, 0, 0, 0);
-      s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[2], qx[4 * i + 2], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[3], qx[4 * i + 3], s1, 0, 0, 0);
+    for (int i0 = 0; i0 < QL / 4; i0 += 4) {
+      f32x16 s0 = {}, s1 = {};
+#pragma unroll
+      for (int i = i0; i < i0 + 4; ++i) {
+        const f32x4 kf = *(const f32x4*)(kt + n * D + 4 * ((2 * i + gsel) ^ (n & 15)));
+        s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[0], qx[4 * i], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[1], qx[4 * i + 1], s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[2], qx[4 * i + 2], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[3], qx[4 * i + 3], s1, 0, 0, 0);
+      }
+      sum = i0 == 0 ? s0 + s1 : sum + (s0 + s1);
+      if (ROPE && D == 128) __builtin_amdgcn_sched_barrier(0);  // (the registers of one group at a time)
     }
-    return s0 + s1;
+    return sum;
   };
 
   if (t_begin < t_end) {
@@ -212,6 +222,7 @@ __global__ void __launch_bounds__(64 * NW, 1) attend_f32_kernel(AttendArgs a) {
     // mask and the tile's maximum (both lane halves of a row)
     const int lim = vlim - t * KT - 4 * gsel;
     float mx = -__builtin_inff();
+    uint32_t seen = 0;  // this lane's visible keys
 #pragma unroll
     for (int j4 = 0; j4 < 4; ++j4) {
       const uint32_t kv = *(const uint32_t*)&sval[slot][8 * j4 + 4 * gsel];
@@ -219,6 +230,7 @@ __global__ void __launch_bounds__(64 * NW, 1) attend_f32_kernel(AttendArgs a) {
       for (int e = 0; e < 4; ++e) {
         const int j = 4 * j4 + e;
         const bool vis = 8 * j4 + e <= lim && ((kv >> (8 * e)) & 0xFFu) != 0;
+        seen |= vis ? 1u << j : 0u;
         s[j] = vis ? s[j] * a.sm_scale : -__builtin_inff();
         mx = fmaxf(mx, s[j]);
       }
@@ -244,13 +256,47 @@ __global__ void __launch_bounds__(64 * NW, 1) attend_f32_kernel(AttendArgs a) {
     }
     l += ls[0] + ls[1];
     typedef float vfrag_t __attribute__((ext_vector_type(DBLK)));
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int r = 8 * (j >> 2) + 4 * gsel + (j & 3);
-      const int d0 = DBLK * n;  // this lane's dims of the row
-      const vfrag_t vf = *(const vfrag_t*)(vs[buf] + r * D + 4 * ((d0 >> 2) ^ (r & 15)) + (d0 & 3));
+    auto value_row = [&](int r, int d0) {
+      return *(const vfrag_t*)(vs[buf] + r * D + 4 * ((d0 >> 2) ^ (r & 15)) + (d0 & 3));
+    };
+    auto add_keys = [&](int j, const vfrag_t& vf) {
 #pragma unroll
       for (int db = 0; db < DBLK; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db], s[j], o[db], 0, 0, 0);
+    };
+    auto values = [&](int j) { return value_row(8 * (j >> 2) + 4 * gsel + (j & 3), DBLK * n); };  // this lane's dims
+    if (__ballot(seen != 0xFFFFu) == 0) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) add_keys(j, values(j));
+      continue;
+    }
+    // Values that are not finite must not reach rows that do not see their key (0 * inf):
+    // in a tile with hidden keys such a pair of keys is added row by row.
+    uint32_t apart = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const vfrag_t vf = values(j);
+      float z = 0.f;
+#pragma unroll
+      for (int db = 0; db < DBLK; ++db) z += vf[db] * 0.f;
+      if (__ballot(z != 0.f)) apart |= 1u << j;
+      else add_keys(j, vf);
+    }
+    while (apart) {
+      const int j = __builtin_ctz(apart);
+      apart &= apart - 1;
+      float pj = s[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) pj = i == j ? s[i] : pj;
+      for (int h = 0; h < 2; ++h) {  // the pair's key of lane half h
+        const float p = __shfl(pj, n + 32 * h);
+        const bool vis = (__shfl((int)seen, n + 32 * h) >> j) & 1;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const vfrag_t vf = value_row(8 * (j >> 2) + 4 * h + (j & 3), DBLK * (8 * (i >> 2) + 4 * gsel + (i & 3)));
+#pragma unroll
+          for (int db = 0; db < DBLK; ++db) o[db][i] += vis ? p * vf[db] : 0.f;
+        }
+      }
     }
   }
 

@@ -3,7 +3,10 @@ not a multiple of 8) over more tiles than the position table holds, odd and even
 row tiles whose last waves have no rows, and lookup entries to skip in each.  Expected values: the oracle,
 at the bars of the other attention cases."""
 import pytest
+import torch
 
+from paper_2402_04617_amd import infllm as F
+from tests.gpu_util import Layer, log
 from tests.test_gpu_kernels import _attend_case
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +47,35 @@ F32_CASES = [
 @pytest.mark.parametrize("mode", ["parts", "one-part", "skipped-entry"])
 def test_chunk_attend_f32_tiles(case, mode):
     _attend_case(case, workspace=mode != "one-part", invalid_entry=mode == "skipped-entry")
+
+
+@pytest.mark.parametrize("D,G,n_q,remap", [(64, 4, 45, False), (128, 1, 70, False), (64, 2, 19, True)])
+def test_f32_hidden_values_stay_hidden(D, G, n_q, remap):
+    """Values that are not finite reach the rows that see their key and no others: a token inside the chunk,
+    and position 0, which stands in for the keys of a skipped lookup entry."""
+    lL, lbs, past, hot = 40, 20, 300, 7
+    p = F.params(G, 1, D, 0, lL, lbs, 2, 4, "f32", rope_inv_freq=F.rope_frequencies(D) if remap else None)
+    S = past + n_q
+    L = Layer(p, 1, S, chunk=n_q, ring=n_q + lL + 1)
+    g = torch.Generator(device="cuda").manual_seed(D + n_q)
+    for t in (L.mem.k, L.mem.v, L.mem.k_rot):
+        if t is not None:
+            t.copy_(torch.randn(t.shape, generator=g, device="cuda"))
+    q = torch.randn((1, G, n_q, D), generator=g, device="cuda")
+    idx = torch.tensor([[[3, 5, 8, 10 ** 6]]], dtype=torch.int32, device="cuda")  # unit 0 is not looked up
+
+    def attend():
+        out, lse = torch.zeros_like(q), torch.zeros((1, G, n_q), device="cuda")
+        log(f"[attend] hidden values D={D} G={G} n_q={n_q} remap={remap}")
+        F.infllm_chunk_attend(p, L.mem.struct, q, n_q * D, n_q, past, idx, 4, out, n_q * D, lse, L.ws)
+        torch.cuda.synchronize()
+        return out, lse
+
+    clean, lse = attend()
+    L.mem.v[:, :, 0] = float("nan")
+    L.mem.v[:, :, past + hot] = float("inf")
+    out, lse2 = attend()
+    assert torch.equal(lse, lse2)
+    # the same products in the same order, but for the sums of the keys taken apart
+    assert (out[:, :, :hot] - clean[:, :, :hot]).abs().max().item() <= 1e-5
+    assert not torch.isfinite(out[:, :, hot:]).any()
