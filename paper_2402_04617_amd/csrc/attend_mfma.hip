@@ -915,7 +915,8 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
     for (int j = 0; j < NI; ++j) load_k(1, off1, j);
 #pragma unroll
     for (int j = 0; j < NI; ++j) load_k(2, off2, j);
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * NI));  // the query rows and K(t0) have landed
+    // the query rows and K(t0) have landed ("memory": the reads of the rows stay behind it)
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * NI) : "memory");
     if (active) read_q();
     lds_barrier();  // K(t0) published, the query rows read
 #pragma unroll
