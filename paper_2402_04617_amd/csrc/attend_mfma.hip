@@ -256,7 +256,8 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   // The wave's query rows go to LDS first, whole rows at a time, into the V buffers
   // (256 rows fill the four exactly; V loads start once they are read back), swizzled
   // like a K tile.  Loading them into registers directly made the compiler wait for
-  // every tile load issued behind them.
+  // every tile load issued behind them.  A part without tiles loads none: nothing of it
+  // waits for them, and the epilogue stages its rows over the V buffers.
   const uint32_t lds_k0 = (uint32_t)(uintptr_t)(INFLLM_LDS bf16_t*)sm.k[0];
   const uint32_t lds_v0 = (uint32_t)(uintptr_t)(INFLLM_LDS bf16_t*)sm.v[0];
   constexpr int NQ = 32 / RPI;  // load instructions for 32 rows
@@ -272,7 +273,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
     h -= wrap ? G : 0;
     i += wrap ? 1 : 0;
   };
-  if (active) {
+  if (active && t_begin < t_end) {
     // within the kv head's query rows 32-bit byte offsets do, unless the heads lie
     // very far apart
     const bf16_t* qg = (const bf16_t*)a.q + (int64_t)(b * a.n_q_heads + g * G) * a.q_head_stride;

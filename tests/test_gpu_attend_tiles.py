@@ -79,3 +79,43 @@ def test_f32_hidden_values_stay_hidden(D, G, n_q, remap):
     # the same products in the same order, but for the sums of the keys taken apart
     assert (out[:, :, :hot] - clean[:, :, :hot]).abs().max().item() <= 1e-5
     assert not torch.isfinite(out[:, :, hot:]).any()
+
+
+@pytest.mark.parametrize("D,Hkv,n_q", [(128, 8, 512), (64, 8, 512), (128, 2, 512)])
+def test_parts_without_tiles(D, Hkv, n_q):
+    """The first chunk of a document, split over the keys: parts that lie past the last key of a row tile's
+    queries hold no tile.  Their rows are zeros with an lse of -inf, whatever the queries are, and queries that
+    are not finite leave the other rows as they were (8 and 4 waves of rows)."""
+    G, rows = 4, 4 * Hkv * n_q
+    p = F.params(G * Hkv, Hkv, D, 128, 4096, 128, 4, 32, "bf16", sm_scale=D ** -0.5)
+    L = Layer(p, 1, n_q, chunk=n_q, ring=n_q + 1)
+    g = torch.Generator(device="cuda").manual_seed(n_q + D)
+    for t in (L.mem.k, L.mem.v):
+        t.copy_(torch.randn(t.shape, generator=g, device="cuda"))
+    q = torch.randn((1, G * Hkv, n_q, D), generator=g, device="cuda").to(L.dt)
+    idx = torch.full((1, Hkv, 32), -1, dtype=torch.int32, device="cuda")
+    # the first rows of every 256-row tile: what a late query load would leave in the staged output rows
+    hot = torch.arange(n_q, device="cuda") % 64 < 4
+
+    def partial(qq):
+        out, lse = torch.zeros_like(q), torch.zeros((1, G * Hkv, n_q), device="cuda")
+        L.ws.fill_(0xA5)
+        log(f"[partial] parts without tiles D={D} Hkv={Hkv} n_q={n_q}")
+        parts = F.infllm_attend_partial(p, L.mem.struct, qq, n_q * D, n_q, 0, idx, 32, out, n_q * D, lse, L.ws)
+        assert parts > 1
+        o = L.ws[:parts * rows * D * 2].view(torch.float16).view(parts, G * Hkv, n_q, D).clone()
+        part_lse = L.ws[parts * rows * D * 2:][:parts * rows * 4].view(torch.float32).view(parts, G * Hkv, n_q).clone()
+        F.infllm_lse_merge(p, 1, n_q, parts, L.ws, out, n_q * D, lse)
+        torch.cuda.synchronize()
+        return o, part_lse, out, lse
+
+    o, part_lse, out, lse = partial(q)
+    empty = part_lse == float("-inf")
+    assert empty.any(0)[:, :64].all() and not empty.all(0).any()
+    assert (o[empty] == 0).all()
+    bad = q.clone()
+    bad[:, :, hot] = float("nan")
+    o2, part_lse2, out2, lse2 = partial(bad)
+    assert (o2[empty & ~hot] == 0).all()
+    assert torch.equal(o2[:, :, ~hot], o[:, :, ~hot]) and torch.equal(part_lse2[:, :, ~hot], part_lse[:, :, ~hot])
+    assert torch.equal(out2[:, :, ~hot], out[:, :, ~hot]) and torch.equal(lse2[:, :, ~hot], lse[:, :, ~hot])
