@@ -407,7 +407,9 @@ bool attend_uses_mfma(const AttendArgs& a) {
 int attend_select_max(const AttendArgs& a) {
   if (attend_uses_mfma(a)) return a.geom.idx_stride <= kFusedSelectMaxK ? kFusedSelectMax : -1;
   const int G = a.n_q_heads / a.n_kv_heads;
-  return a.geom.n_q > 0 && decode_eligible(a.bf16, a.geom.n_q, G, a.geom.n_sel) ? kDecodeSelMax : -1;
+  if (a.geom.n_q == 0 || !decode_eligible(a.bf16, a.geom.n_q, G, a.geom.n_sel)) return -1;
+  // (of a row of at most n_sel units every unit is looked up, and nothing is selected)
+  return a.geom.n_sel <= kWaveSelMaxK ? kDecodeSelMax : a.geom.n_sel;
 }
 
 hipError_t launch_attend(const AttendArgs& a, hipStream_t s) {

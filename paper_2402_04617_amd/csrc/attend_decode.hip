@@ -137,8 +137,8 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(Attend
   const int mem_len = sq.mem_len, parts_mem = sq.parts_mem;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane % LPK, r = lane / LPK;  // 16-byte piece of the row, key slot of the load
-  // Lookup: from idx, or (idx_out set: rows of at most kDecodeSelMax scores) selected
-  // here by the first wave of every workgroup -- a launch fewer before the keys can be
+  // Lookup: from idx, or (idx_out set: rows of at most kDecodeSelMax scores, at most
+  // kWaveSelMaxK units or all of them) selected here by the first wave of every workgroup -- a launch fewer before the keys can be
   // read -- and written out by part 0.
   const bool select = a.idx_out != nullptr;
   const bool sel_all = geo.n_sel == 0 || geo.n_sel == geo.n_units;
@@ -228,7 +228,8 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(Attend
   if (select && !sel_all && wave == 0) {
 #pragma unroll
     for (int j = 0; j < tk::kWavePer; ++j) wkey[j] = tk::order_key(__uint_as_float(wkey[j]));
-    tk::wave_select<tk::kWavePer>(wkey, geo.n_units, geo.n_sel, sidx, wsm);
+    if (!tk::wave_select<tk::kWavePer>(wkey, geo.n_units, geo.n_sel, sidx, wsm))
+      tk::wave_select_exact<tk::kWavePer>(wkey, geo.n_units, geo.n_sel, sidx);
   }
   __syncthreads();
   if (select && part == 0) {

@@ -92,6 +92,7 @@ struct Smem {
   bf16_t v[NBUF][KB * D];
   uint32_t rows[kRowTable];  // store position of each key group of a window of tiles (kNoRow: skipped entry)
   int32_t sidx[kSelLds];    // the lookup row (its first kSelLds entries)
+  int32_t sel_ok;           // whether the first wave's select wrote it
   uint8_t kvalid[NBUF][KB];
 };
 
@@ -240,7 +241,8 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   const bool sel_writer = SEL > 0 && rt == 0 && part == 0;
   const bool sel_here = SEL > 0 && (sel_writer || units_here);
   const bool sel_all = geo.n_sel == 0 || geo.n_sel == geo.n_units;  // every unit (or none) is looked up
-  const bool sel_waves = SEL == 2 || geo.n_sel <= tk::kWaveK;       // by single waves
+  // by single waves, or by the radix select of all of them
+  const bool sel_waves = SEL > 2 ? tk::long_select_fits<tk::kWavePer>(geo.n_units, geo.n_sel) : geo.n_sel <= tk::kWaveK;
   const float* srow = SEL > 0 ? a.sel_scores + (int64_t)bg * a.sel_stride : nullptr;
   // scores of the single-wave select: short rows in the first wave, 16 per lane; long
   // rows 16 per lane of every wave (loaded before the queries, whose latency overlaps)
@@ -252,6 +254,12 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
     for (int j = 0; j < WPER; ++j)
       wkey[j] = __float_as_uint(srow[min(wave * tk::kWaveRow + 64 * j + lane, geo.n_units - 1)]);
   }
+  uint32_t skey[SEL > 0 ? SEL : 1] = {};  // scores of the radix select, SEL per thread
+  auto load_radix_keys = [&]() {
+#pragma unroll
+    for (int j = 0; j < SEL; ++j) skey[j] = tk::order_key(srow[min(tid + j * tk::kThreads, geo.n_units - 1)]);
+  };
+  if (SEL == 2 && sel_here && !sel_all && !sel_waves) load_radix_keys();
 
   // The wave's query rows go to LDS first, whole rows at a time, into the V buffers
   // (256 rows fill the four exactly; V loads start once they are read back), swizzled
@@ -330,28 +338,29 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
       if constexpr (SEL > 2) {
         done = tk::long_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::LongSelSmem*)sm.rows);
       } else {
-        if (wave == 0)
-          tk::wave_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::WaveSelSmem*)sm.rows);
-        done = true;
+        if (wave == 0) {
+          const bool ok = tk::wave_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::WaveSelSmem*)sm.rows);
+          if (lane == 0) sm.sel_ok = ok;
+        }
+        lds_barrier();
+        done = sm.sel_ok != 0;
       }
     }
-    if constexpr (SEL > 2) if (!done) {
-      // more units than the waves' select takes, or too many ties: the radix select,
-      // SEL keys per thread, filtered first (the filter declines, uniformly, when the
-      // bound it finds leaves more than a thread's worth of candidates)
-      constexpr int SK = SEL;
-      uint32_t skey[SK];
-#pragma unroll
-      for (int j = 0; j < SK; ++j) skey[j] = tk::order_key(srow[min(tid + j * tk::kThreads, geo.n_units - 1)]);
+    if constexpr (SEL > 0) if (!done) {
+      // more units than the waves' select takes, or too many candidates: the radix select,
+      // SEL keys per thread, long rows filtered first (the filter declines, uniformly, when
+      // the bound it finds leaves more than a thread's worth of candidates)
+      if (SEL > 2 || sel_waves) load_radix_keys();
       auto valid = [&](int j) { return tid + j * tk::kThreads < geo.n_units; };
       auto index = [&](int j) { return tid + j * tk::kThreads; };
       uint32_t thr;
       int rem;
       bool ge;
-      done = geo.n_sel <= tk::kThreads && tk::filtered_select<SK>(skey, geo.n_units, geo.n_sel, sm.sidx);
+      if constexpr (SEL > 2)
+        done = geo.n_sel <= tk::kThreads && tk::filtered_select<SEL>(skey, geo.n_units, geo.n_sel, sm.sidx);
       if (!done) {
-        tk::radix_threshold<SK>(skey, valid, geo.n_sel, thr, rem, ge);
-        tk::write_selection<SK>(skey, valid, index, thr, rem, ge, geo.n_sel, sm.sidx);
+        tk::radix_threshold<SEL>(skey, valid, geo.n_sel, thr, rem, ge);
+        tk::write_selection<SEL>(skey, valid, index, thr, rem, ge, geo.n_sel, sm.sidx);
       }
     }
     lds_barrier();

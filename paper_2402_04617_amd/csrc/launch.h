@@ -138,6 +138,12 @@ constexpr int kDecodeMinKeysPerWg = 128;
 constexpr int kDecodeMaxSel = 1024;
 // Longest score row the decode kernel selects from itself (one wave).
 constexpr int kDecodeSelMax = 1024;
+// Most units a wave selects by ranking its candidates (see topk_select.h): about
+// 64 ln(64 / (64 - k)) keys of a full row are left, 89 at 48, 107 at 52 and 133 at 56, and a
+// wave ranks 128.  Past it the eight waves of a workgroup share a radix select, which the
+// decode kernel (four waves) leaves to a launch of its own: by the one wave alone, bit by bit,
+// it takes 11 us (64 units of 217 for one sequence at 32K: 36.3 us per step).
+constexpr int kWaveSelMaxK = 48;
 
 // Score rows the matrix-core attention selects from itself: rows of at most
 // kFusedSelectShort units hold two keys per thread, longer rows up to

@@ -10,28 +10,7 @@ using tk::kThreads;
 using tk::kWaves;
 using tk::kMaxPer;
 
-// Rows of up to tk::kWaveRow scores: one wave per row.
-__global__ void __launch_bounds__(64) topk_short_kernel(const float* __restrict__ scores, int stride, int n_all, int k,
-                                                        int32_t* __restrict__ idx, const TopkRows tr, int var_on) {
-  const int row = blockIdx.x, l = threadIdx.x;
-  const int n = var_on ? tr.row_n[row / tr.rows_per_seq] : n_all;
-  int32_t* out = idx + (int64_t)row * k;
-  const int k_eff = min(k, n);
-  for (int j = k_eff + l; j < k; j += 64) out[j] = -1;
-  if (k_eff == 0) return;
-  if (k_eff == n) {
-    for (int j = l; j < n; j += 64) out[j] = j;
-    return;
-  }
-  __shared__ tk::WaveSelSmem sm;
-  uint32_t key[tk::kWavePer];
-  tk::load_wave_keys(scores + (int64_t)row * stride, n, key);
-#pragma unroll
-  for (int j = 0; j < tk::kWavePer; ++j) key[j] = tk::order_key(__uint_as_float(key[j]));
-  tk::wave_select<tk::kWavePer>(key, n, k_eff, out, sm);
-}
-
-// Longer rows.  PER: keys per thread of the common path (0: radix select only).
+// PER: keys per thread of the common path (0: radix select only).
 // Rows of a variable-length batch (var_on): row r holds tr.row_n[r / rows_per_seq]
 // scores; n is then the largest of them.  Rows are `stride` floats apart.
 template <int PER>
@@ -48,9 +27,11 @@ __global__ void __launch_bounds__(kThreads) topk_kernel(const float* __restrict_
   __shared__ int wave_tot[kWaves];
   if constexpr (PER > 0) {
     if (k_eff < n) {
-      // up to kWaveK units: the waves' candidates, reduced once more by the first wave;
-      // the radix select otherwise, and where too many scores tie
-      if (k_eff <= tk::kWaveK) {
+      // Long rows, few units: the waves' candidates, reduced once more by the first wave (32 of
+      // 2,000 scores 6.0 -> 5.2 us, of 8,155 7.8 -> 6.7); the radix select otherwise, and where
+      // too many keys crowd.  In a launch of its own a row that one wave could hold gains
+      // nothing from it (16 of 216 scores 4.0 to 4.2 us either way, 32 of 987 4.5).
+      if (PER > 2 && tk::long_select_fits<PER>(n, k_eff)) {
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         __shared__ tk::LongSelSmem sel;
         uint32_t key[PER];
@@ -73,8 +54,8 @@ static hipError_t launch_topk(int rows, const float* scores, int stride, int n_m
   const int per = (n_max + kThreads - 1) / kThreads;
   const dim3 grid(rows), block(kThreads);
 #define INFLLM_TOPK(P) hipLaunchKernelGGL(topk_kernel<P>, grid, block, 0, s, scores, stride, n_max, k, idx, tr, var_on)
-  if (n_max <= tk::kWaveRow)
-    hipLaunchKernelGGL(topk_short_kernel, grid, dim3(64), 0, s, scores, stride, n_max, k, idx, tr, var_on);
+  if (per <= 1) INFLLM_TOPK(1);
+  else if (per <= 2) INFLLM_TOPK(2);
   else if (per <= 4) INFLLM_TOPK(4);
   else if (per <= 8) INFLLM_TOPK(8);
   else if (per <= kMaxPer) INFLLM_TOPK(kMaxPer);

@@ -351,18 +351,17 @@ __device__ bool filtered_select(const uint32_t (&key)[PER], int n, int k_eff, in
 // rank themselves by counting.  No histogram, no atomics, no barrier: in the
 // attention's prologue, where the whole workgroup waits for the lookup, 32 of 987
 // scores are loaded and selected in 2.9 us where the radix select of eight waves
-// took 4.6 (8,155 scores, by all waves: 12.3 -> 6.1 us); as a launch of its own
-// 4.5 -> 4.0 us (7.1 -> 6.1).
-constexpr int kWaveK = 48;      // most units selected this way (at 64 the bound is the smallest lane maximum,
-                                // which leaves too many candidates: 6.2 against 4.4 us at 987 scores)
-constexpr int kWaveCand = 128;  // most candidates a wave ranks
+// took 4.6 (8,155 scores, by all waves: 12.3 -> 6.1 us).
+constexpr int kWaveK = kWaveSelMaxK;
+constexpr int kWaveCand = 128;  // most candidates a wave ranks: two per lane
 
-// A bound T on the k-th largest lane value: at least k of the 64 values are >= T
-// (its low bits are zero; 0 when fewer than k values are nonzero).
-__device__ __forceinline__ uint32_t lane_bound(uint32_t mx, int k) {
-  uint32_t T = 0;
+// A bound T on the k-th largest lane value: at least k of the 64 values are >= T (0
+// when fewer than k values are nonzero).  Raises T, found from the bits above HI, by
+// the bits HI .. LO; the lower ones stay zero.
+template <int HI, int LO>
+__device__ __forceinline__ uint32_t lane_bound(uint32_t mx, int k, uint32_t T = 0) {
 #pragma unroll
-  for (int s = 30; s >= 16; s -= 2) {
+  for (int s = HI - 1; s >= LO; s -= 2) {
     const uint32_t t1 = T | (1u << s), t2 = T | (2u << s), t3 = T | (3u << s);
     const int c1 = __popcll(__ballot(mx >= t1)), c2 = __popcll(__ballot(mx >= t2)), c3 = __popcll(__ballot(mx >= t3));
     T = c3 >= k ? t3 : c2 >= k ? t2 : c1 >= k ? t1 : T;
@@ -445,19 +444,11 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
-// One wave, any k_eff < n: the k_eff-th largest key bit by bit over all keys, then the
-// keys above it and the first equal ones, in index order.
+// One wave, T the k_eff-th largest of its n keys: the keys above T and the first
+// equal ones, in index order.
 template <int PER>
-__device__ __forceinline__ void wave_select_exact(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out) {
+__device__ __forceinline__ void write_above(const uint32_t (&key)[PER], int n, int k_eff, uint32_t T, int32_t* __restrict__ out) {
   const int l = threadIdx.x & 63;
-  uint32_t T = 0;
-  for (int s = 31; s >= 0; --s) {
-    const uint32_t t = T | (1u << s);
-    int c = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) c += __popcll(__ballot(l + 64 * j < n && key[j] >= t));
-    T = c >= k_eff ? t : T;
-  }
   int equal = k_eff;  // keys equal to T to keep
 #pragma unroll
   for (int j = 0; j < PER; ++j) equal -= __popcll(__ballot(l + 64 * j < n && key[j] > T));
@@ -473,28 +464,57 @@ __device__ __forceinline__ void wave_select_exact(const uint32_t (&key)[PER], in
     seen += __popcll(me);
   }
 }
+// One wave, any k_eff < n: the k_eff-th largest key bit by bit over all keys (11 us for
+// 1,024 keys: where no other wave can help, and the candidates are too many).
+template <int PER>
+__device__ __forceinline__ void wave_select_exact(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out) {
+  const int l = threadIdx.x & 63;
+  uint32_t T = 0;
+  for (int s = 31; s >= 0; --s) {
+    const uint32_t t = T | (1u << s);
+    int c = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) c += __popcll(__ballot(l + 64 * j < n && key[j] >= t));
+    T = c >= k_eff ? t : T;
+  }
+  write_above<PER>(key, n, k_eff, T, out);
+}
 
 // One wave: the k_eff largest of n <= 64*PER keys (lane l: element l + 64*j),
-// 0 < k_eff < n.
+// 0 < k_eff < n, k_eff <= kWaveK.  False (nothing written; the same in every lane) where
+// more than kWaveCand keys are left that do not just tie.
 typedef Candidates<kWaveCand> WaveSelSmem;
 template <int PER>
-__device__ __forceinline__ void wave_select(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out,
+__device__ __forceinline__ bool wave_select(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out,
                                             WaveSelSmem& sm) {
   const int l = threadIdx.x & 63;
-  if (k_eff <= kWaveK) {
-    auto valid = [&](int j) { return l + 64 * j < n; };
-    const uint32_t T = lane_bound(lane_max<PER>(key, valid), k_eff);
+  auto valid = [&](int j) { return l + 64 * j < n; };
+  auto candidates = [&](uint32_t T) {
 #pragma unroll
     for (int j = 0; j < kWaveCand; j += 64) sm.key[j + l] = 0u;
     wave_lds_fence();
-    const int n_cand = compact_candidates<PER>(key, valid, [&](int j) { return l + 64 * j; }, T, 0, sm);
+    const int c = compact_candidates<PER>(key, valid, [&](int j) { return l + 64 * j; }, T, 0, sm);
     wave_lds_fence();
-    if (n_cand <= kWaveCand) {
-      rank_candidates(sm, n_cand, k_eff, out);
-      return;
+    return c;
+  };
+  const uint32_t mx = lane_max<PER>(key, valid);
+  uint32_t T = lane_bound<31, 16>(mx, k_eff);
+  int n_cand = candidates(T);
+  if (n_cand > kWaveCand) {
+    // scores that differ in their low bits only: the whole bound, a lane maximum
+    T = lane_bound<15, 0>(mx, k_eff, T);
+    int above = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) above += __popcll(__ballot(valid(j) && key[j] > T));
+    if (above < k_eff) {  // the k-th largest key itself: massive ties
+      write_above<PER>(key, n, k_eff, T, out);
+      return true;
     }
+    n_cand = candidates(T);
+    if (n_cand > kWaveCand) return false;
   }
-  wave_select_exact<PER>(key, n, k_eff, out);  // many units, or too many ties at the bound
+  rank_candidates(sm, n_cand, k_eff, out);
+  return true;
 }
 constexpr int kWavePer = 16;                 // keys per lane of the single-wave select
 constexpr int kWaveRow = 64 * kWavePer;      // longest row it takes
@@ -510,6 +530,13 @@ __device__ __forceinline__ void load_wave_keys(const float* __restrict__ s, int 
 // hundred candidates, which the first wave reduces once more and ranks.  False
 // (workgroup-uniform) when too many keys tie.  Ends with a barrier.
 constexpr int kLongCand = 512;
+// Whether so few candidates are to be expected: a lane keeps -ln(1 - k/64) of its keys on
+// average.  (48 of 8,155 scores leave about 700: a selection launch took 10.2 us with the vain
+// attempt and takes 8.3 by the filtered radix select alone; 48 of 5,000 7.5, and 8.2 there.)
+template <int PER>
+__device__ __forceinline__ bool long_select_fits(int n, int k) {
+  return k <= kWaveK && (float)n * __logf(64.f / (float)(64 - k)) <= (float)(PER * (kLongCand - 64));
+}
 struct LongSelSmem {
   Candidates<kLongCand> all;
   WaveSelSmem last;
@@ -523,7 +550,7 @@ __device__ __forceinline__ bool long_select(const uint32_t (&key)[PER], int n, i
   const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int e0 = wave * 64 * PER + l;
   auto valid = [&](int j) { return e0 + 64 * j < n; };
-  const uint32_t Tw = lane_bound(lane_max<PER>(key, valid), k_eff);
+  const uint32_t Tw = lane_bound<31, 16>(lane_max<PER>(key, valid), k_eff);
   if (l == 0) sm.bound[wave] = Tw;
   __syncthreads();
   uint32_t T = 0;
@@ -553,7 +580,7 @@ __device__ __forceinline__ bool long_select(const uint32_t (&key)[PER], int n, i
       k2[j] = valid2(j) ? sm.all.key[l + 64 * j] - 1u : 0u;
       i2[j] = sm.all.idx[l + 64 * j];
     }
-    const uint32_t T2 = max(T, lane_bound(lane_max<P2>(k2, valid2), k_eff));
+    const uint32_t T2 = max(T, lane_bound<31, 16>(lane_max<P2>(k2, valid2), k_eff));
 #pragma unroll
     for (int j = 0; j < kWaveCand; j += 64) sm.last.key[j + l] = 0u;
     wave_lds_fence();
