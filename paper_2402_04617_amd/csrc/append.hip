@@ -31,6 +31,7 @@
 #include <cstring>
 
 #include "qsum.h"
+#include "ring_slot.h"
 #include "unit_build.h"
 
 namespace infllm {
@@ -238,8 +239,7 @@ __device__ __forceinline__ void thin_scan_block(const AppendArgs& a, int blk, fl
           for (int h = 0; h < G; ++h) x[i] += (double)Elem<T>::load(qb + h * a.q_head_stride + (int64_t)i * D);
           const int64_t t = past + i - a.n_local;
           if (t >= a.n_init && t < past) {
-            const int sp = slot0 + i - (slot0 + i >= a.ring ? a.ring : 0);
-            const int st = sp - a.n_local + (sp < a.n_local ? a.ring : 0);  // n_local < ring
+            const int st = leaving_slot(past + i, a.n_local, a.n_init, ring_slot(slot0, i, a.ring), a.ring);
             ht[i] = col[(int64_t)st * D];
             kt[i] = Elem<T>::load(kread + ((int64_t)bg * a.capacity + t) * D + d);
           }
@@ -262,14 +262,14 @@ __device__ __forceinline__ void thin_scan_block(const AppendArgs& a, int blk, fl
         raw_tot += (float)x[i];
         if (ROPE) x[i] = rot_lane(x[i], past + i);
         run += x[i];
-        const int sp = slot0 + i - (slot0 + i >= a.ring ? a.ring : 0);
+        const int sp = ring_slot(slot0, i, a.ring);
         col[(int64_t)sp * D] = run;
         const int64_t t = past + i - a.n_local;
         if (t >= a.n_init) {
           double h = ht[i], k = kt[i];
           if (t >= past) {
             // token of this chunk: its running sum was written by this thread above
-            const int st = sp - a.n_local + (sp < a.n_local ? a.ring : 0);
+            const int st = leaving_slot(past + i, a.n_local, a.n_init, sp, a.ring);
             h = col[(int64_t)st * D];
             k = Elem<T>::load((const T*)a.k_src + (int64_t)bg * a.kv_head_stride + (t - past) * D + d);
           }
@@ -363,8 +363,9 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
 #pragma unroll
   for (int e = 0; e < kDPT; ++e) carry[e] = base[e];
   // (no barrier: the slots this launch writes, positions past .. past + n_q - 1, never
-  // alias slot past - 1 or the slots of the tokens t = p - l_L it reads, since the host
-  // checked ring >= l_L + n_q; so the base loads stay in flight with the tile's loads)
+  // alias slot past - 1 or, where any token leaves the window, the slots of the tokens
+  // t = p - l_L it reads: the host then checked that the ring still holds them all once
+  // the chunk is appended; so the base loads stay in flight with the tile's loads)
 
   constexpr int GQ = GT > 0 ? GT : 1;  // query pieces loaded up front per position
   constexpr int NP = kDPT / 2;          // dimension pairs (double2) per thread
@@ -393,8 +394,7 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
 #pragma unroll
       for (int s = 0; s < kSeg; ++s) {
         const int ic = min(t0 + seg * kSeg + s, a.n_q - 1);
-        const int sp = slot0 + ic - (slot0 + ic >= a.ring ? a.ring : 0);
-        const int st = sp - a.n_local + (sp < a.n_local ? a.ring : 0);  // n_local < ring
+        const int st = leaving_slot(past + ic, a.n_local, a.n_init, ring_slot(slot0, ic, a.ring), a.ring);
         slot_t[s] = st;
         const double2* src = (const double2*)(ring + (int64_t)st * D);
 #pragma unroll
@@ -483,7 +483,7 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
       if (ROPE && early) rotate_d(kt, past + i - a.n_local, d0 / 2, a.rope);
       part[s] = 0.0;
       if (i < a.n_q) {
-        const int slot = slot0 + i - (slot0 + i >= a.ring ? a.ring : 0);
+        const int slot = ring_slot(slot0, i, a.ring);
         double2* d2 = (double2*)(ring + (int64_t)slot * D);
 #pragma unroll
         for (int e = 0; e < NP; ++e) {
@@ -525,8 +525,8 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
         const int ic = min(i0 + s, a.n_q - 1);
         int64_t t = past + ic - a.n_local;
         t = t < 0 ? 0 : t;
-        const int sp = slot0 + ic - (slot0 + ic >= a.ring ? a.ring : 0);
-        const int st = sp - a.n_local + (sp < a.n_local ? a.ring : 0);  // n_local < ring
+        const int sp = ring_slot(slot0, ic, a.ring);
+        const int st = leaving_slot(past + ic, a.n_local, a.n_init, sp, a.ring);
         st_t[s] = st;
 #pragma unroll
         for (int e = 0; e < NP; ++e) {

@@ -47,3 +47,35 @@ def test_append_tiles(dtype, G, D, lL, chunks):
             exp = w.reshape(B, Hkv, D // 8, 8).sum(-1)
             assert np.allclose(part[:, :, :, t % ring], exp, rtol=1e-10, atol=1e-10), t
         past += n
+
+
+@pytest.mark.parametrize("dtype,G,D,lL,chunks", [
+    ("bf16", 4, 128, 4096, (32, 32, 9)),        # a slice per wave
+    ("bf16", 3, 64, 700, (100, 513, 8)),        # whole blocks, a second tile
+    ("f32", 2, 128, 300, (100, 60, 3, 130)),    # a window shorter than a tile
+])
+def test_append_ring_shorter_than_window(dtype, G, D, lL, chunks):
+    """Short chunks at the start of a stream need no ring slot of a token that leaves the window: a ring that
+    holds one chunk is accepted, and only the running sums are written."""
+    rng = np.random.default_rng(lL + 1)
+    Hkv, lI, S, ring = 2, 5, sum(chunks), max(chunks) + 1
+    assert ring <= lL and S <= lI + lL
+    p = F.params(G * Hkv, Hkv, D, lI, lL, 64, 2, 2, dtype)
+    q, k, v = rand_inputs(rng, G * Hkv, Hkv, S, D, dtype)
+    L = Layer(p, 1, S, chunk=max(chunks), ring=ring)
+    L.mem.rpart.fill_(3.0)
+    qd, kd, vd = dev(q, dtype), dev(k, dtype), dev(v, dtype)
+    pref = np.cumsum(q.astype(np.float64).reshape(1, Hkv, G, S, D).sum(axis=2), axis=2)
+    past = 0
+    for n in chunks:
+        log(f"[append short ring] {dtype} G={G} D={D} l_L={lL} ring={ring} past={past} n={n}")
+        off = past * D * L.esize
+        F.infllm_append(p, L.mem.struct, qd.data_ptr() + off, S * D, kd.data_ptr() + off, vd.data_ptr() + off, S * D,
+                        n, past)
+        torch.cuda.synchronize()
+        got = host(L.mem.qprefix)
+        for t in range(past, past + n):
+            assert np.allclose(got[:, :, t % ring], pref[:, :, t], rtol=1e-12, atol=1e-12), t
+        past += n
+    assert (L.mem.rpart == 3.0).all()
+    assert np.array_equal(host(L.mem.k)[:, :, :S], k) and np.array_equal(host(L.mem.v)[:, :, :S], v)
