@@ -267,7 +267,7 @@ __device__ __forceinline__ void thin_scan_block(const AppendArgs& a, int blk, fl
         const int64_t t = past + i - a.n_local;
         if (t >= a.n_init) {
           double h = ht[i], k = kt[i];
-          if (t >= past) {
+          if (leaving_key_in_chunk(past, t, a.n_init)) {
             // token of this chunk: its running sum was written by this thread above
             const int st = leaving_slot(past + i, a.n_local, a.n_init, sp, a.ring);
             h = col[(int64_t)st * D];
@@ -523,8 +523,7 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
 #pragma unroll
       for (int s = 0; s < kSeg; ++s) {
         const int ic = min(i0 + s, a.n_q - 1);
-        int64_t t = past + ic - a.n_local;
-        t = t < 0 ? 0 : t;
+        const int64_t t = past + ic - a.n_local;
         const int sp = ring_slot(slot0, ic, a.ring);
         const int st = leaving_slot(past + ic, a.n_local, a.n_init, sp, a.ring);
         st_t[s] = st;
@@ -533,9 +532,9 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
           hp[s][e] = ((const double2*)(ring + (int64_t)sp * D))[e];
           hq[s][e] = ((const double2*)(ring + (int64_t)st * D))[e];
         }
-        kk[s] = t >= past
+        kk[s] = leaving_key_in_chunk(past, t, a.n_init)
                     ? load_rawd<T>((const T*)a.k_src + (int64_t)bg * a.kv_head_stride + (t - past) * D + d0)
-                    : load_rawd<T>(kread + ((int64_t)bg * a.capacity + t) * D + d0);
+                    : load_rawd<T>(kread + ((int64_t)bg * a.capacity + (t < 0 ? 0 : t)) * D + d0);
       }
 #pragma unroll
       for (int s = 0; s < kSeg; ++s) {

@@ -1,4 +1,5 @@
-// Slots of the append's rings (position t lies in slot t mod ring).
+// Slots of the append's rings (position t lies in slot t mod ring), and where it reads the
+// keys of the tokens that leave the window.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -18,6 +19,12 @@ __host__ __device__ inline int ring_slot(int slot0, int i, int ring) {
 __host__ __device__ inline int leaving_slot(int64_t pos, int n_local, int n_init, int sp, int ring) {
   if (pos - n_local < n_init) return sp;
   return sp - n_local + (sp < n_local ? ring : 0);
+}
+// Whether the key of token t that leaves the window is read from the chunk (which may be
+// absent where the caller stored it before): only where t has scores, which the host then
+// checked it is given for.  Any other key comes from the store, its value used or not.
+__host__ __device__ inline bool leaving_key_in_chunk(int64_t past, int64_t t, int n_init) {
+  return t >= past && t >= n_init;
 }
 
 }  // namespace infllm

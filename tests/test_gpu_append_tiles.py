@@ -79,3 +79,35 @@ def test_append_ring_shorter_than_window(dtype, G, D, lL, chunks):
         past += n
     assert (L.mem.rpart == 3.0).all()
     assert np.array_equal(host(L.mem.k)[:, :, :S], k) and np.array_equal(host(L.mem.v)[:, :, :S], v)
+
+
+@pytest.mark.parametrize("dtype,lI,lL,chunks", [
+    ("bf16", 5, 300, (100, 90, 110)),   # the first chunk lies within the window
+    ("f32", 200, 8, (20, 90, 60)),      # ... within the initial tokens
+    ("bf16", 0, 513, (513, 12)),
+])
+def test_append_of_stored_keys(dtype, lI, lL, chunks):
+    """k and v absent: the caller has stored them, and no token of a chunk leaves the window inside it."""
+    rng = np.random.default_rng(lL + 2)
+    Hkv, G, D, S = 2, 4, 64, sum(chunks)
+    ring = lL + max(chunks) + 1
+    p = F.params(G * Hkv, Hkv, D, lI, lL, 64, 2, 2, dtype)
+    q, k, v = rand_inputs(rng, G * Hkv, Hkv, S, D, dtype)
+    L = Layer(p, 1, S, chunk=max(chunks), ring=ring)
+    qd = dev(q, dtype)
+    L.mem.k.copy_(dev(k, dtype))
+    L.mem.v.copy_(dev(v, dtype))
+    pref = np.cumsum(q.astype(np.float64).reshape(1, Hkv, G, S, D).sum(axis=2), axis=2)
+    past = 0
+    for n in chunks:
+        log(f"[append stored] {dtype} l_I={lI} l_L={lL} past={past} n={n}")
+        F.infllm_append(p, L.mem.struct, qd.data_ptr() + past * D * L.esize, S * D, None, None, 0, n, past)
+        torch.cuda.synchronize()
+        got, part = host(L.mem.qprefix), host(L.mem.rpart)
+        for t in range(past, past + n):
+            assert np.allclose(got[:, :, t % ring], pref[:, :, t], rtol=1e-12, atol=1e-12), t
+        for pos in range(max(past, lI + lL), past + n):
+            t = pos - lL
+            w = k[:, :, t].astype(np.float64) * (pref[:, :, pos] - pref[:, :, t])
+            assert np.allclose(part[:, :, :, t % ring], w.reshape(1, Hkv, D // 8, 8).sum(-1), rtol=1e-10, atol=1e-10), t
+        past += n

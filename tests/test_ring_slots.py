@@ -1,6 +1,7 @@
 """The append's ring slots on the host: over every accepted combination of past length, chunk, window, initial
 tokens and ring of a small range (rings shorter than the window among them), each slot lies in the ring, and a
-token that has scores is read from the slot that holds it."""
+token that has scores is read from the slot that holds it; and the chunk's keys are read only where the call has to
+give them."""
 import os
 import shutil
 import subprocess
@@ -26,11 +27,17 @@ int main() {
             if (t_hi > t_lo && t_lo + ring < past + n_q) continue;
             ++cases;
             shorter += ring <= n_local;
+            const bool need_k = t_hi > t_lo && t_hi > past;  // the chunk's keys may be absent otherwise
             for (int i = 0; i < n_q; ++i) {
               const int sp = ring_slot(past % ring, i, ring), st = leaving_slot(past + i, n_local, n_init, sp, ring);
               const int t = past + i - n_local;
               if (sp != (past + i) % ring || st < 0 || st >= ring || (t >= n_init && st != t % ring)) {
                 std::printf("ring %d n_q %d l_L %d l_I %d past %d i %d: %d %d\n", ring, n_q, n_local, n_init, past, i, sp, st);
+                return 1;
+              }
+              const bool chunk = leaving_key_in_chunk(past, t, n_init);
+              if ((chunk && !need_k) || (t >= n_init && chunk != (t >= past)) || t >= past + n_q) {
+                std::printf("key: n_q %d l_L %d l_I %d past %d i %d\n", n_q, n_local, n_init, past, i);
                 return 1;
               }
             }
