@@ -105,10 +105,7 @@ RopeArgs rope_args(const infllm_params* p, bool positions, bool memory) {
   const double two_pi = 6.283185307179586476925286766559;
   for (int i = 0; i < p->head_dim / 2; ++i) {
     const double th = p->rope_inv_freq[i];
-    if (positions) {
-      const double turns = th / two_pi, whole = std::floor(turns);
-      r.rev[i] = (uint64_t)((turns - whole) * 0x1p64);  // the difference is exact and below 1
-    }
+    if (positions) r.rev[i] = th / two_pi;
     if (memory) {
       r.mem_cos[i] = (float)std::cos((double)p->n_local * th);
       r.mem_sin[i] = (float)std::sin((double)p->n_local * th);

@@ -302,7 +302,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
     }
   }
   // The lane's rotary table entries under the remap (granule lane % CH, four pairs)
-  uint64_t rev[4];
+  double rev[4];
   float mcos[4], msin[4];
   if (remap) {
 #pragma unroll
@@ -497,8 +497,8 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   // their LDS rows like K fragments.  Under the remap the rows are turned in place
   // first, by R(l_L) for a memory part and to their own positions for a local one:
   // a lane takes one granule of one query and turns it for all of the query's heads,
-  // so that each angle's sine and cosine are formed once (per row and lane, with
-  // float64 angles, this took 4.5 us of a local part's prologue).
+  // so that each angle's sine and cosine are formed once (per row and lane they took
+  // 4.5 us of a local part's prologue).
   bf16x8 qreg[KSTEPS];
   auto read_q = [&]() {
     if (remap) {

@@ -96,21 +96,19 @@ __device__ __forceinline__ int div_by(int n, const FastDiv& f) {
 constexpr int kMaxPairs = 64;  // D/2 at D = 128
 struct RopeArgs {
   int32_t on;                // 0: positions pre-applied, nothing is rotated
-  uint64_t rev[kMaxPairs];   // theta_i / (2 pi) mod 1 in units of 2^-64: revolutions per position of pair i
+  double rev[kMaxPairs];     // theta_i / (2 pi): revolutions per position of pair i
   float mem_cos[kMaxPairs];  // cos(l_L theta_i)
   float mem_sin[kMaxPairs];  // sin(l_L theta_i)
 };
 
-// cos and sin of p * theta_i, rev = r.rev[i].  Whole revolutions drop out of the
-// fixed-point product by itself: its top 32 fraction bits are two 32-bit multiplies
-// (positions fit 32 bits: the store holds them all), within 2^-32 + p * 2^-65
-// revolutions of the exact angle -- closer than a float64 product at a million
-// positions, and several times cheaper.  The hardware sine and cosine take
-// revolutions.
-__device__ __forceinline__ void rope_cos_sin(uint64_t rev, int64_t pos, float& c, float& s) {
-  const uint32_t p = (uint32_t)pos;
-  const uint32_t t = __umulhi(p, (uint32_t)rev) + p * (uint32_t)(rev >> 32);
-  const float f = (float)t * 0x1p-32f;
+// cos and sin of p * theta_i, rev = r.rev[i].  The angle is reduced to [0, 1) revolutions in
+// float64 (p * theta_i reaches 10^6 radians at a million positions), so that it is right to
+// 2^-36 revolutions there and to float32's own rounding below; the hardware sine and cosine
+// take revolutions.
+__device__ __forceinline__ void rope_cos_sin(double rev, int64_t pos, float& c, float& s) {
+  double t = (double)pos * rev;
+  t -= floor(t);
+  const float f = (float)t;
   s = __builtin_amdgcn_sinf(f);
   c = __builtin_amdgcn_cosf(f);
 }

@@ -189,3 +189,31 @@ def test_remap_stream_bf16_chunks_then_decode():
     q, k, v = rand_inputs(rng, 8, 2, S, D, "bf16", qk_std=1.0)
     steps = [(s, chunk) for s in range(0, S0, chunk)] + [(S0 + i, 1) for i in range(6)]
     _stream(p, q, k, v, steps, {2, 5, 8, 9, 12, 14}, chunk, "bf16", 1e-3)
+
+
+@pytest.mark.parametrize("chunks", [(300,), (40, 8, 1)], ids=["scan", "thin"])
+def test_small_angles_keep_their_bits(chunks):
+    """Angles down to 2^-33 revolutions: the key (1, 0) of a pair turns to (cos, sin), whose sine is as small as
+    the angle.  A float32 angle is within 2^-24 of its size, and the sine of so small an angle follows it; the bar
+    leaves the hardware sine 2^-16."""
+    D, S = 128, sum(chunks)
+    turns = 2.0 ** -np.linspace(9, 33, D // 2)
+    p = F.params(2, 2, D, 0, 512, 64, 2, 2, "f32", rope_inv_freq=list(2 * np.pi * turns))
+    L = Layer(p, 1, S, chunk=max(chunks), ring=600)
+    q = torch.ones((1, 2, S, D), device="cuda")
+    k = torch.zeros((1, 2, S, D), device="cuda")
+    k[..., 0::2] = 1.0
+    past = 0
+    for n in chunks:
+        log(f"[remap angles] past={past} n={n}")
+        off = past * D * 4
+        F.infllm_append(p, L.mem.struct, q.data_ptr() + off, S * D, k.data_ptr() + off, k.data_ptr() + off, S * D, n, past)
+        past += n
+    torch.cuda.synchronize()
+    got = host(L.mem.k_rot)[0, :, 1:S].astype(np.float64)
+    ang = 2 * np.pi * np.arange(1, S)[:, None] * turns
+    err = np.abs(got[..., 1::2] / np.sin(ang) - 1)
+    small = np.broadcast_to(ang < 0.4, err.shape)
+    print("largest relative error of a sine", err[small].max())
+    assert err[small].max() <= 2.0 ** -16
+    assert np.abs(got[..., 0::2] - np.cos(ang)).max() <= 2e-6
