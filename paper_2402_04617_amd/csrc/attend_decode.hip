@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) attend_decode_kernel(Attend
   if (select && !sel_all && wave == 0) {
 #pragma unroll
     for (int j = 0; j < tk::kWavePer; ++j) wkey[j] = tk::order_key(__uint_as_float(wkey[j]));
-    if (!tk::wave_select<tk::kWavePer>(wkey, geo.n_units, geo.n_sel, sidx, wsm))
+    if (!tk::wave_select<tk::kWavePer, true>(wkey, geo.n_units, geo.n_sel, sidx, wsm))
       tk::wave_select_exact<tk::kWavePer>(wkey, geo.n_units, geo.n_sel, sidx);
   }
   __syncthreads();

@@ -329,7 +329,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   } else if (sel_here) {
     // (the select's scratch lies in the position table, filled after it)
     static_assert(sizeof(tk::LongSelSmem) <= sizeof(sm.rows) && sizeof(tk::WaveSelSmem) <= sizeof(sm.rows), "scratch");
-    bool done = sel_all;
+    bool done = sel_all, published = false;
     if (sel_all) {
       for (int u = tid; u < geo.n_sel; u += 64 * NWAVE) sm.sidx[u] = u;
     } else if (sel_waves) {
@@ -339,14 +339,14 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
         done = tk::long_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::LongSelSmem*)sm.rows);
       } else {
         if (wave == 0) {
-          const bool ok = tk::wave_select<WPER>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::WaveSelSmem*)sm.rows);
+          const bool ok = tk::wave_select<WPER, false>(wkey, geo.n_units, geo.n_sel, sm.sidx, *(tk::WaveSelSmem*)sm.rows);
           if (lane == 0) sm.sel_ok = ok;
         }
         lds_barrier();
-        done = sm.sel_ok != 0;
+        done = published = sm.sel_ok != 0;
       }
     }
-    if constexpr (SEL > 0) if (!done) {
+    if constexpr (SEL > 0) if (__builtin_expect(!done, 0)) {
       // more units than the waves' select takes, or too many candidates: the radix select,
       // SEL keys per thread, long rows filtered first (the filter declines, uniformly, when
       // the bound it finds leaves more than a thread's worth of candidates)
@@ -363,7 +363,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
         tk::write_selection<SEL>(skey, valid, index, thr, rem, ge, geo.n_sel, sm.sidx);
       }
     }
-    lds_barrier();
+    if (!published) lds_barrier();
     if (sel_writer) {
       int32_t* orow = a.idx_out + (int64_t)bg * geo.idx_stride;
       for (int u = tid; u < geo.idx_stride; u += 64 * NWAVE) orow[u] = u < geo.n_sel ? sm.sidx[u] : -1;

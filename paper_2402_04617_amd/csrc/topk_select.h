@@ -482,9 +482,12 @@ __device__ __forceinline__ void wave_select_exact(const uint32_t (&key)[PER], in
 
 // One wave: the k_eff largest of n <= 64*PER keys (lane l: element l + 64*j),
 // 0 < k_eff < n, k_eff <= kWaveK.  False (nothing written; the same in every lane) where
-// more than kWaveCand keys are left that do not just tie.
+// more than kWaveCand keys are left.  CROWDED: not before scores that differ in their low
+// bits only, and massive ties, are tried too (where no faster select follows; the
+// matrix-core prologue has the radix select for them, and the longer code cost a step of
+// four sequences of 24 tokens 0.7 of its 43.8 us).
 typedef Candidates<kWaveCand> WaveSelSmem;
-template <int PER>
+template <int PER, bool CROWDED>
 __device__ __forceinline__ bool wave_select(const uint32_t (&key)[PER], int n, int k_eff, int32_t* __restrict__ out,
                                             WaveSelSmem& sm) {
   const int l = threadIdx.x & 63;
@@ -500,8 +503,9 @@ __device__ __forceinline__ bool wave_select(const uint32_t (&key)[PER], int n, i
   const uint32_t mx = lane_max<PER>(key, valid);
   uint32_t T = lane_bound<31, 16>(mx, k_eff);
   int n_cand = candidates(T);
-  if (n_cand > kWaveCand) {
-    // scores that differ in their low bits only: the whole bound, a lane maximum
+  if (__builtin_expect(n_cand > kWaveCand, 0)) {
+    if constexpr (!CROWDED) return false;
+    // the whole bound, a lane maximum
     T = lane_bound<15, 0>(mx, k_eff, T);
     int above = 0;
 #pragma unroll
