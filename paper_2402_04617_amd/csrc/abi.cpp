@@ -15,7 +15,7 @@
 using namespace infllm;
 
 namespace infllm {
-int attend_max_parts(bool bf16, int G, int n_q, int64_t max_virtual);
+int attend_max_parts(bool bf16, int G, int head_dim, int n_q, int64_t max_virtual);
 }
 
 namespace {
@@ -217,8 +217,8 @@ infllm_status prepare_attend(const infllm_params* p, const infllm_memory* m, con
   const size_t per_part = rows > 0 ? (size_t)rows * part_row_bytes(p) : 1;
   const int max_parts = (workspace == nullptr) ? 0 : (int)(workspace_bytes / per_part > 4096 ? 4096 : workspace_bytes / per_part);
   int row_waves = 0;
-  int parts = attend_choose_parts(bf16, m->batch, p->n_q_heads, p->n_kv_heads, n_q, n_sel, (int)n_virtual,
-                                  max_parts, &row_waves);
+  int parts = attend_choose_parts(bf16, m->batch, p->n_q_heads, p->n_kv_heads, p->head_dim, n_q, n_sel,
+                                  (int)n_virtual, max_parts, &row_waves);
   if (parts < 1) return INFLLM_E_WORKSPACE;
   // With the remap, memory keys (I and the units) and local keys go to
   // different parts, in proportion to their counts.
@@ -477,7 +477,7 @@ static size_t mass_part_bytes(const infllm_params* p, int32_t batch, int32_t n_q
 size_t infllm_workspace_bytes(const infllm_params* p, int32_t batch, int32_t n_q) {
   if (check_params(p) != INFLLM_OK || batch < 1 || n_q < 0) return 0;
   const int G = p->n_q_heads / p->n_kv_heads;
-  int parts = attend_max_parts(p->dtype == INFLLM_BF16, G, n_q, max_virtual_keys(p, n_q));
+  int parts = attend_max_parts(p->dtype == INFLLM_BF16, G, p->head_dim, n_q, max_virtual_keys(p, n_q));
   if (remap(p)) parts = std::max(parts, 2);
   size_t a = attend_ws_bytes(p, batch, n_q, parts);
   size_t b = qbar_ws_bytes(p, batch, n_q);

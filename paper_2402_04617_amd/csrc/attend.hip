@@ -346,19 +346,55 @@ bool decode_eligible(bool bf16, int n_q, int G, int n_sel) {
 
 }  // namespace
 
-// Key parts of the decode kernel: enough workgroups for the whole chip, but at
-// least kDecodeMinKeysPerWg keys each.
-int attend_decode_parts(int bh, int n_virtual) {
-  const int by_chip = (kDecodeTargetWgs + bh - 1) / bh;
-  const int by_keys = max(1, n_virtual / kDecodeMinKeysPerWg);
-  return max(1, min(by_chip, by_keys));
+// Most key parts of the decode kernel: of kDecodeMinWork keys * head_dim each.
+static int decode_most_parts(int head_dim, int64_t n_virtual) {
+  return (int)max((int64_t)1, min((int64_t)kDecodeTargetWgs, n_virtual * head_dim / kDecodeMinWork));
 }
 
-int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int n_q, int n_sel, int n_virtual,
-                        int max_parts, int* row_waves) {
+// Key parts of the decode kernel: a short context whole, else the cheapest of the counts
+// that just fit one or two workgroups per compute unit (and 8 and 16, which the merge joins
+// in one and two passes).  In eighths of a tile: 3.5 tiles for each round of workgroups (their
+// prologues and epilogues), half the tiles of a wave with and half without the padding of
+// its buffers, and the merge.  Swept over 1 to 72 (sequence, kv head) pairs, groups of 1, 4
+// and 8, 512 to 6,400 keys of 64 and 128 dims: within 1.5 % of the best count on average
+// (parts of at least 256 keys for two workgroups per unit: 13 %; of 128: 8 %, and up to 40 %
+// off where a few more workgroups than fit began a round of their own).
+int attend_decode_parts(int bh, int G, int head_dim, int n_virtual) {
+  if ((int64_t)n_virtual * head_dim * (G + 2) <= kDecodeWholeWork) return 1;
+  const int most = decode_most_parts(head_dim, n_virtual);
+  // many pairs: the count that just passes the target (where it leaves half the chip with one
+  // workgroup fewer, only for long contexts: 200 pairs of 8,350 keys 186 us as 600 workgroups,
+  // 200 as 400; of 1,100 keys 45 and 42)
+  const int pass = (kDecodeTargetWgs + bh - 1) / bh;
+  if (bh > kDecodeTargetWgs / 2 || (3 * bh > kDecodeTargetWgs && n_virtual >= 4096))
+    return max(1, min(pass, n_virtual / 256));
+  const int fit2 = kDecodeTargetWgs / bh, fit1 = kDecodeTargetWgs / 2 / bh;
+  const int tile = decode_step_keys(head_dim);  // of all waves
+  int best = 1, best_cost = 0;
+  for (const int c : {1, 8, 16, fit1, fit2}) {
+    int p = min(c, min(fit2, most));
+    const int tiles = (n_virtual + p * tile - 1) / (p * tile);
+    const bool few = tiles <= kDecodeShortTiles;
+    // (no more for two workgroups per unit than fill the buffers of their waves)
+    if (few && p > fit1) p = max(fit1, (n_virtual + kDecodeShortTiles * tile - 1) / (kDecodeShortTiles * tile));
+    const int padded = few ? kDecodeShortTiles : (tiles + 2) / 3 * 3;
+    const int rounds = (bh * p + kDecodeTargetWgs / 2 - 1) / (kDecodeTargetWgs / 2);
+    const int cost = 28 * rounds + 4 * padded + (int)((int64_t)4 * n_virtual / (p * tile)) + (p > 1 ? 24 : 0) +
+                     (p > 8 ? 16 : 0) + (p > 16 ? 4 : 0);
+    if (best_cost == 0 || cost <= best_cost) {
+      best = p;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int head_dim, int n_q, int n_sel,
+                        int n_virtual, int max_parts, int* row_waves) {
   *row_waves = kMfmaWaves;
   const int G = n_q_heads / n_kv_heads;
-  if (decode_eligible(bf16, n_q, G, n_sel)) return min(attend_decode_parts(batch * n_kv_heads, n_virtual), max(1, max_parts));
+  if (decode_eligible(bf16, n_q, G, n_sel))
+    return min(attend_decode_parts(batch * n_kv_heads, G, head_dim, n_virtual), max(1, max_parts));
   const int R = G * n_q;
   const int key_tile = bf16 ? 64 : kF32Keys;
   const int n_tiles = (n_virtual + key_tile - 1) / key_tile;
@@ -394,8 +430,9 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
   return best;
 }
 
-int attend_max_parts(bool bf16, int G, int n_q, int64_t max_virtual) {
-  if (decode_eligible(bf16, n_q, G, 0)) return attend_decode_parts(1, (int)max_virtual);
+// (an upper bound, for any batch)
+int attend_max_parts(bool bf16, int G, int head_dim, int n_q, int64_t max_virtual) {
+  if (decode_eligible(bf16, n_q, G, 0)) return decode_most_parts(head_dim, max_virtual);
   return bf16 ? 8 : 16;
 }
 

@@ -24,7 +24,6 @@
 namespace infllm {
 namespace {
 
-constexpr int kDecodeWaves = 4;
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 // v + (the value of v in the lanes given by the DPP control), one VALU op.
@@ -418,9 +417,7 @@ template <int D>
 hipError_t launch_decode_d(const AttendArgs& a, hipStream_t s) {
   const int G = a.n_q_heads / a.n_kv_heads;
   const dim3 grid(a.parts * a.batch * a.n_kv_heads), block(64 * kDecodeWaves);
-  // tiles of a wave (2 loads of 64 / (D/8) keys each), as the kernel cuts them
-  const int tk_keys = 2 * 64 / (D / 8), waves = a.parts * kDecodeWaves;
-  const bool few = a.geom.n_virtual <= 4 * tk_keys * waves;
+  const bool few = a.geom.n_virtual <= kDecodeShortTiles * decode_step_keys(D) * a.parts;
 #define INFLLM_DECODE(GG)                                                                                      \
   do {                                                                                                         \
     if (few) hipLaunchKernelGGL((attend_decode_kernel<D, GG, 4>), grid, block, 0, s, a);                        \

@@ -129,10 +129,20 @@ hipError_t launch_select_topk_var(int rows, const float* scores, int stride, int
 constexpr int kMfmaWaves = 8;
 constexpr int kMfmaTargetWgs = 256;
 // Workgroups the bf16 decode kernel aims for (two per compute unit), and the
-// fewest keys it gives one workgroup (one sequence at 32K, 6,265 keys: 25 parts of
-// 256 keys 14.9 us, 50 of 128 13.5; the merge takes either in 4.3).
+// fewest keys * head_dim it gives one workgroup (64 keys of 128 dims).
 constexpr int kDecodeTargetWgs = 512;
-constexpr int kDecodeMinKeysPerWg = 128;
+constexpr int kDecodeMinWork = 64 * 128;
+constexpr int kDecodeWaves = 4;
+// Keys that its waves take at a time: a tile of two loads of 64 / (head_dim / 8) keys each;
+// up to so many tiles of a wave are all in flight at once.
+constexpr int decode_step_keys(int head_dim) { return kDecodeWaves * 2 * 64 / (head_dim / 8); }
+constexpr int kDecodeShortTiles = 4;
+// Work of a short context (keys * head_dim * (group + 2): the keys' bytes and the group's
+// products) up to which one workgroup takes all its keys: the merge's launch costs more than
+// a split saves (337 keys of 64 dims, group 2, four sequences: 11.4 us per step, split 14.1).
+// Either way costs the same at 1,024 keys of 64 dims and 512 of 128 (group 1), 430 of 64
+// (group 4) and about 215 of 128.
+constexpr int64_t kDecodeWholeWork = 192000;
 // Most selected units the decode kernel stages in LDS; longer lookups decode on
 // the matrix-core kernel.
 constexpr int kDecodeMaxSel = 1024;
@@ -239,8 +249,8 @@ __host__ __device__ inline SeqStep seq_step(const AttendArgs& a, int b) {
 }
 // Number of key parts the attention uses for this shape, limited by max_parts, and
 // for the matrix-core kernel the waves of a workgroup that hold rows.
-int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int n_q, int n_sel, int n_virtual,
-                        int max_parts, int* row_waves);
+int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int head_dim, int n_q, int n_sel,
+                        int n_virtual, int max_parts, int* row_waves);
 hipError_t launch_attend(const AttendArgs& a, hipStream_t s);
 // Most scores a row may hold for the launch to select its units itself (see
 // AttendArgs::idx_out); -1 where its kernel never does.

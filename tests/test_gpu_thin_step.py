@@ -120,3 +120,56 @@ def test_thin_step_varlen(n_q):
             assert torch.equal(s1, scores[b, :, :units[b]])
         assert float((o1[0].float() - out[b].float()).abs().max()) <= 3e-2
         assert float((l1[0] - lse[b]).abs().max()) <= 1e-3
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,keys", [(5, 8, 8, 128, 4201), (3, 4, 8, 128, 8400), (9, 8, 4, 64, 1101),
+                                            (5, 8, 1, 64, 3001), (1, 8, 4, 128, 6400), (22, 8, 1, 64, 1400)])
+def test_decode_parts_fit_the_chip(B, Hkv, G, D, keys):
+    """No part count whose last few workgroups begin a round of their own (two to a compute unit, 512 in all)
+    while a context is short enough for their rounds to show; the rows of the parts merged are those of one part."""
+    p = F.params(G * Hkv, Hkv, D, 4, 16384, 32, 2, 4, "bf16", sm_scale=D ** -0.5)
+    gen = torch.Generator(device="cuda").manual_seed(keys)
+    L = Layer(p, B, keys, chunk=1)
+    for t in (L.mem.k, L.mem.v):
+        t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+    q = torch.randn((B, G * Hkv, 1, D), generator=gen, device="cuda").to(L.dt)
+    idx = torch.full((B, Hkv, 4), -1, dtype=torch.int32, device="cuda")
+    out, lse = torch.zeros_like(q), torch.zeros((B, G * Hkv, 1), device="cuda")
+    one, lse1 = torch.zeros_like(q), torch.zeros_like(lse)
+    log(f"[decode parts] B={B} Hkv={Hkv} G={G} D={D} keys={keys}")
+    parts = F.infllm_attend_partial(p, L.mem.struct, q, D, 1, keys - 1, idx, 4, out, D, lse, L.ws)
+    assert parts > 1 and parts * B * Hkv <= 512
+    F.infllm_lse_merge(p, B, 1, parts, L.ws, out, D, lse)
+    F.infllm_chunk_attend(p, L.mem.struct, q, D, 1, keys - 1, idx, 4, one, D, lse1, None)
+    torch.cuda.synchronize()
+    # partial rows are rounded to 11 bits, outputs to 8
+    assert float((out.float() - one.float()).abs().max()) <= 2.0 ** -7 * float(one.float().abs().max())
+    assert float((lse - lse1).abs().max()) <= 1e-5 * max(1.0, float(lse1.abs().max()))
+
+
+#        G, D, most keys that one workgroup takes whole
+@pytest.mark.parametrize("G,D,whole", [(1, 64, 1000), (2, 64, 750), (1, 128, 500), (4, 128, 250), (8, 128, 150)])
+def test_short_context_decode_parts(G, D, whole):
+    """Decoding over a short context: one part, which needs no merge, up to where a split pays; the same rows on
+    both sides of the line as in one part."""
+    Hkv, B = 2, 2
+    p = F.params(G * Hkv, Hkv, D, 4, 4096, 32, 2, 4, "bf16", sm_scale=D ** -0.5)
+    gen = torch.Generator(device="cuda").manual_seed(whole)
+    L = Layer(p, B, whole + 300, chunk=1)
+    for t in (L.mem.k, L.mem.v):
+        t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+    q = torch.randn((B, G * Hkv, 1, D), generator=gen, device="cuda").to(L.dt)
+    idx = torch.full((B, Hkv, 4), -1, dtype=torch.int32, device="cuda")
+    for keys in (1, 337, whole, whole + 1, whole + 257):
+        log(f"[short decode] G={G} D={D} keys={keys}")
+        out, lse = torch.zeros_like(q), torch.zeros((B, G * Hkv, 1), device="cuda")
+        one, lse1 = torch.zeros_like(q), torch.zeros_like(lse)
+        parts = F.infllm_attend_partial(p, L.mem.struct, q, D, 1, keys - 1, idx, 4, out, D, lse, L.ws)
+        assert keys == whole + 1 or (parts == 1) == (keys <= whole), keys
+        if parts > 1:
+            F.infllm_lse_merge(p, B, 1, parts, L.ws, out, D, lse)
+        F.infllm_chunk_attend(p, L.mem.struct, q, D, 1, keys - 1, idx, 4, one, D, lse1, None)
+        torch.cuda.synchronize()
+        # partial rows are rounded to 11 bits, outputs to 8
+        assert float((out.float() - one.float()).abs().max()) <= 2.0 ** -7 * float(one.float().abs().max())
+        assert float((lse - lse1).abs().max()) <= 1e-5 * max(1.0, float(lse1.abs().max()))
