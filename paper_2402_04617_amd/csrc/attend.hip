@@ -401,13 +401,18 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
   const int cap = min(bf16 ? 8 : 16, min(max(1, n_tiles / 2), max(1, max_parts)));
   // Both kernels put one wave on a SIMD's matrix core (float32) or eight on a compute
   // unit's (bf16) at a time, so a part count that starts a new round of workgroups for a few of
-  // them is worse than a lower one.  A round costs its longest part plus kPartCost
-  // tiles (prologue and epilogue), and any split the merge, kMergeCost tiles.  (56 row
+  // them is worse than a lower one.  A workgroup costs its tiles plus kPartCost (prologue and
+  // epilogue), and any split the merge, kMergeCost tiles.  (56 row
   // tiles of 108 key tiles, a 389-query chunk: 5 parts, 280 workgroups, 84.5 us per
   // step; 4 parts, 224 workgroups, 63.8 us.  A 300-token prompt: 2 parts 25.4 us, 1
   // part and no merge 22.9 us.)
+  // The row tiles of a chunk see the keys up to their last query, and the longest start
+  // first, so that in several rounds long workgroups are followed by short ones: r rounds
+  // end after r workgroups of the size in their middle, or the longest.  (A prompt of 1,500
+  // tokens, 8 kv heads of group 8: 376 workgroups of 1 part 86 us, 752 of 2 parts 97.)
   constexpr int kPartCost = 5, kMergeCost = 3;
-  int best = 1, best_cost = 0;
+  int best = 1;
+  int64_t best_cost = 0;
   // (costs in quarters of a tile of a full workgroup; a half-filled bf16 workgroup,
   // one wave per SIMD, takes about kHalfTile/4 of that tile's time: a 300-token
   // prompt as 80 half-filled workgroups 17.7 us per step, as 40 full ones 21)
@@ -418,8 +423,12 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
     const int per_round = bf16 ? kMfmaTargetWgs : kMfmaTargetWgs * 4 / waves;
     const int tile_cost = half || R <= 32 * kMfmaWaves / 2 ? kHalfTile : 4;
     for (int p = 1; p <= cap; ++p) {
-      const int rounds = (row_tiles * p + per_round - 1) / per_round;
-      const int cost = rounds * (4 * kPartCost + (tile_cost * n_tiles + p - 1) / p) + (p > 1 ? 4 * kMergeCost : 0);
+      const int64_t wgs = (int64_t)row_tiles * p, rounds = (wgs + per_round - 1) / per_round;
+      auto wg_cost = [&](int64_t tiles) { return 4 * kPartCost + (tile_cost * tiles + p - 1) / p; };
+      const int64_t after = max((int64_t)0, wgs - rounds * per_round / 2);  // workgroups after the middle one
+      const int64_t mid_tiles = (n_virtual - n_q + n_q * after / wgs) / key_tile + 1;
+      const int64_t middle = rounds == 1 ? 0 : rounds * wg_cost(min((int64_t)n_tiles, mid_tiles));
+      const int64_t cost = max(wg_cost(n_tiles), middle) + (p > 1 ? 4 * kMergeCost : 0);
       if ((half == 0 && p == 1) || cost < best_cost) {
         best = p;
         best_cost = cost;

@@ -119,3 +119,27 @@ def test_parts_without_tiles(D, Hkv, n_q):
     assert (o2[empty & ~hot] == 0).all()
     assert torch.equal(o2[:, :, ~hot], o[:, :, ~hot]) and torch.equal(part_lse2[:, :, ~hot], part_lse[:, :, ~hot])
     assert torch.equal(out2[:, :, ~hot], out[:, :, ~hot]) and torch.equal(lse2[:, :, ~hot], lse[:, :, ~hot])
+
+
+@pytest.mark.parametrize("Hkv,G,n_q,B,past", [(8, 8, 1500, 1, 0), (8, 4, 3000, 3, 0), (8, 8, 1500, 1, 300)])
+def test_long_prompt_is_not_split(Hkv, G, n_q, B, past):
+    """A prompt with more row tiles than compute units: the short row tiles follow the long ones, and a split of
+    the keys (which starts more workgroups than it shortens) and its merge are not worth it."""
+    D = 128
+    p = F.params(G * Hkv, Hkv, D, 128, 4096, 128, 4, 32, "bf16", sm_scale=D ** -0.5)
+    L = Layer(p, B, past + n_q, chunk=n_q, ring=n_q + 1)
+    g = torch.Generator(device="cuda").manual_seed(n_q)
+    for t in (L.mem.k, L.mem.v):
+        t.copy_(torch.randn(t.shape, generator=g, device="cuda"))
+    q = torch.randn((B, G * Hkv, n_q, D), generator=g, device="cuda").to(L.dt)
+    idx = torch.full((B, Hkv, 32), -1, dtype=torch.int32, device="cuda")
+    out, lse = torch.zeros_like(q), torch.zeros((B, G * Hkv, n_q), device="cuda")
+    log(f"[prompt] Hkv={Hkv} G={G} n_q={n_q} B={B} past={past}")
+    assert F.infllm_attend_partial(p, L.mem.struct, q, n_q * D, n_q, past, idx, 32, out, n_q * D, lse, L.ws) == 1
+    torch.cuda.synchronize()
+    b, h = B - 1, G + 1  # one head against float32
+    x, k, v = (t.float() for t in (q[b, h], L.mem.k[b, h // G, :past + n_q], L.mem.v[b, h // G, :past + n_q]))
+    z = (x @ k.T * D ** -0.5).masked_fill(torch.arange(past + n_q, device="cuda")[None] >
+                                          past + torch.arange(n_q, device="cuda")[:, None], float("-inf"))
+    assert float((z.softmax(-1) @ v - out[b, h].float()).abs().max()) <= 2e-2
+    assert float((z.logsumexp(-1) - lse[b, h]).abs().max()) <= 1e-3
