@@ -407,9 +407,11 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
   // step; 4 parts, 224 workgroups, 63.8 us.  A 300-token prompt: 2 parts 25.4 us, 1
   // part and no merge 22.9 us.)
   // The row tiles of a chunk see the keys up to their last query, and the longest start
-  // first, so that in several rounds long workgroups are followed by short ones: r rounds
-  // end after r workgroups of the size in their middle, or the longest.  (A prompt of 1,500
-  // tokens, 8 kv heads of group 8: 376 workgroups of 1 part 86 us, 752 of 2 parts 97.)
+  // first, so that in several rounds long workgroups are followed by short ones: unsplit, r
+  // rounds end after r workgroups of the size in their middle, or the longest.  (A prompt of
+  // 1,500 tokens, 8 kv heads of group 8: 376 workgroups of 1 part 86 us, 752 of 2 parts 97.
+  // Splits are charged their longest part each round: by their middle, a 1M chunk would run
+  // as two rounds of half the keys, 333 us instead of 326.)
   constexpr int kPartCost = 5, kMergeCost = 3;
   int best = 1;
   int64_t best_cost = 0;
@@ -425,10 +427,12 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
     for (int p = 1; p <= cap; ++p) {
       const int64_t wgs = (int64_t)row_tiles * p, rounds = (wgs + per_round - 1) / per_round;
       auto wg_cost = [&](int64_t tiles) { return 4 * kPartCost + (tile_cost * tiles + p - 1) / p; };
-      const int64_t after = max((int64_t)0, wgs - rounds * per_round / 2);  // workgroups after the middle one
-      const int64_t mid_tiles = (n_virtual - n_q + n_q * after / wgs) / key_tile + 1;
-      const int64_t middle = rounds == 1 ? 0 : rounds * wg_cost(min((int64_t)n_tiles, mid_tiles));
-      const int64_t cost = max(wg_cost(n_tiles), middle) + (p > 1 ? 4 * kMergeCost : 0);
+      int64_t cost = rounds * wg_cost(n_tiles) + (p > 1 ? 4 * kMergeCost : 0);
+      if (p == 1 && rounds > 1) {
+        const int64_t after = max((int64_t)0, wgs - rounds * per_round / 2);  // workgroups after the middle one
+        const int64_t mid_tiles = (n_virtual - n_q + n_q * after / wgs) / key_tile + 1;
+        cost = max(wg_cost(n_tiles), rounds * wg_cost(min((int64_t)n_tiles, mid_tiles)));
+      }
       if ((half == 0 && p == 1) || cost < best_cost) {
         best = p;
         best_cost = cost;
