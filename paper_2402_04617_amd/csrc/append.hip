@@ -43,9 +43,10 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kSeg = 2;                        // positions per thread per tile: a 512-position chunk is one tile
 constexpr int kTile = (kThreads / 2) * kSeg;   // positions per scan tile
 // Chunks this short fit one wave's 32 segments: each wave of a scan block then takes a
-// slice of its own (with a block per slice, four sequences of 24 tokens took 512 mostly
-// idle blocks in rounds: 57.1 us per step, 51.8 with 64; one thread per dim, as for at
-// most kThinMaxQ positions: 70.6).
+// slice of its own, where a block per slice would not fit the chip at once (four sequences
+// of 24 tokens took 512 mostly idle blocks in rounds: 57.1 us per step, 51.8 with 64; one
+// thread per dim, as for at most kThinMaxQ positions: 70.6; but one sequence of 64 tokens,
+// 128 slices, appends in 5.7 us with a block each and in 8.4 with 16).
 constexpr int kWaveTile = 32 * kSeg;
 constexpr int kCopyPerThread = 4;              // 16-byte vectors per thread in copy blocks
 constexpr int kThinMaxQ = 8;                   // chunks this short take the one-thread-per-dim scan
@@ -287,8 +288,9 @@ __device__ __forceinline__ void thin_scan_block(const AppendArgs& a, int blk, fl
 
 // GT: the query group size G when known at compile time (0: read it at run time).
 // ROPE: the positional remap is on (a.rope.on), fixed at compile time so that
-// the plain path carries none of its code.
-template <typename T, int GT, int DT, bool ROPE>
+// the plain path carries none of its code.  TILES: the chunk has several scan tiles, whose
+// loads run ahead (with one, the code without: 300 tokens 7.4 -> 7.0 us, 512 9.1 -> 8.8).
+template <typename T, int GT, int DT, bool ROPE, bool TILES>
 __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArgs ba, AppendGrid grid,
                                                           float* __restrict__ qbar) {
   const int D = a.head_dim;
@@ -407,9 +409,9 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
   };
   load_queries(0);
   load_leaving(0);
-  for (int t0 = 0; t0 < a.n_q; t0 += kTile) {
+  for (int t0 = 0; t0 < (TILES ? a.n_q : 1); t0 += kTile) {
     const int i0 = t0 + seg * kSeg;
-    const bool early = is_early(t0), more = t0 + kTile < a.n_q;
+    const bool early = is_early(t0), more = TILES && t0 + kTile < a.n_q;
     double run[kSeg][kDPT];
     double tot[kDPT];
 #pragma unroll
@@ -508,8 +510,8 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
 #pragma unroll
     for (int e = 0; e < kDPT; ++e) carry[e] += tile_tot[e];
     if (more) load_leaving(t0 + kTile);
-    if (early) lds_barrier();  // wave_tot may be written again
-    else __syncthreads();      // ... and this tile's slots are read below
+    if (!early) __syncthreads();   // this tile's slots are read below
+    else if (TILES) lds_barrier();  // wave_tot may be written again
 
     // Otherwise the partial representative scores of the tokens t = p - l_L
     // (t >= l_I) of this tile's positions p are formed now: both running sums are
@@ -672,12 +674,17 @@ static hipError_t launch_append_d(const AppendArgs& a, const BuildArgs& ba, cons
   if (blocks == 0) return hipSuccess;
   const dim3 grid(blocks);
   const int G = a.n_q_heads / a.n_kv_heads;
+  const bool tiles = a.n_q > kTile;
 #define INFLLM_APPEND(T, GT)                                                                        \
   do {                                                                                             \
-    if (a.rope.on)                                                                                 \
-      hipLaunchKernelGGL((append_kernel<T, GT, DT, true>), grid, dim3(kThreads), 0, s, a, ba, g, qbar);  \
+    if (a.rope.on && tiles)                                                                        \
+      hipLaunchKernelGGL((append_kernel<T, GT, DT, true, true>), grid, dim3(kThreads), 0, s, a, ba, g, qbar);   \
+    else if (a.rope.on)                                                                            \
+      hipLaunchKernelGGL((append_kernel<T, GT, DT, true, false>), grid, dim3(kThreads), 0, s, a, ba, g, qbar);  \
+    else if (tiles)                                                                                \
+      hipLaunchKernelGGL((append_kernel<T, GT, DT, false, true>), grid, dim3(kThreads), 0, s, a, ba, g, qbar);  \
     else                                                                                           \
-      hipLaunchKernelGGL((append_kernel<T, GT, DT, false>), grid, dim3(kThreads), 0, s, a, ba, g, qbar); \
+      hipLaunchKernelGGL((append_kernel<T, GT, DT, false, false>), grid, dim3(kThreads), 0, s, a, ba, g, qbar); \
   } while (0)
   if (a.bf16) {
     switch (G) {
@@ -710,7 +717,7 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t s, float* qbar, const 
   g.qsum_parts = score_qbar_parts(a.n_q_heads / a.n_kv_heads, a.n_q);
   g.n_qsum = (a.mean_repr && qbar != nullptr && a.n_q > 0) ? g.qsum_parts * a.batch * a.n_kv_heads : 0;
   const int n_slices = a.batch * a.n_kv_heads * (a.head_dim / kRpartDims);
-  g.wave_slices = a.n_q <= kWaveTile;
+  g.wave_slices = a.n_q <= kWaveTile && n_slices > kMfmaTargetWgs;
   g.n_scan = (a.n_q <= 0 || a.mean_repr) ? 0
              : g.thin ? (a.batch * a.n_kv_heads * a.head_dim + kThreads - 1) / kThreads
              : g.wave_slices ? (n_slices + kWaves - 1) / kWaves
