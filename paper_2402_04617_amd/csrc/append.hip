@@ -377,7 +377,9 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a, BuildArg
   // written.  Loads use clamped indices (the values of inactive positions are never
   // used).  A tile's loads are issued as soon as the registers of the tile before are
   // free -- its queries before that tile's scan -- so that a chunk of several tiles
-  // waits for memory once (2,048 positions: 36 us with each tile's loads at its top).
+  // waits for memory once (2,048 positions: 27.5 us with each tile's loads at its top, 25.3
+  // so, within a 1M-context step 36 and 25; of two tiles 1,024 positions 15.0 and 14.7, but
+  // 700 11.5 and 12.5).
   RawD<T> qr[kSeg][GQ];
   double2 ht[kSeg][NP];
   RawD<T> kr[kSeg];
