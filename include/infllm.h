@@ -294,7 +294,9 @@ infllm_status infllm_unit_mass(const infllm_params* p, const infllm_memory* m, c
  * With bf16 chunks (the matrix-core attention), at most 8,192 units and k_m at
  * most 1,024, stages 4 and 5 share one launch: the attention selects the units
  * from the scores itself and writes idx as stage 4 would (same entries, order
- * and padding).
+ * and padding).  So they do with one bf16 token per sequence (1, 2, 4 or 8 query
+ * heads per kv head), at most 1,024 units and k_m at most 48, or no more units
+ * than k_m; and with at most 8 tokens and no units to build, stages 2 and 3 do.
  * units_built is the number of units built by earlier steps (0 for the first
  * step); afterwards n_units(past_len) units are built.  Every stage is validated
  * before the first is enqueued. */

@@ -36,6 +36,9 @@ constexpr int kF32Sel = 2048;  // lookup entries kept in LDS
 //  O^T += V^T P^T: B = the probabilities as S^T leaves them (k-step (a, b) pairs
 //    keys 8a + b and 8a + 4 + b, one per lane half), A = V rows from LDS; output
 //    block db holds dims DBLK*m + db, so that one read feeds all DBLK blocks.
+// In tiles of units the first wave's search for the keys of the tile after next waits for
+// the tile just requested (a lookup entry lies in LDS or in memory and is read through one
+// pointer), so only the other waves run ahead there.
 // Rows of an LDS tile are XOR-swizzled by granule, which makes both reads
 // conflict-free.  What bounds it: the matrix cores' float32 rate (64 cycles per
 // instruction); with one wave per SIMD the softmax (expf, 16 scores per lane and

@@ -11,8 +11,8 @@
 // holds its score and reuses it as the weight of the same key's value piece.
 //
 // The virtual key axis of each (sequence, kv head) is split by cost into `parts`
-// workgroups (the host picks enough parts to give every compute unit two
-// workgroups), and each workgroup's keys evenly over its 4 waves, in whole
+// workgroups (the host picks the parts by rounds of workgroups, one or two to a
+// compute unit), and each workgroup's keys evenly over its 4 waves, in whole
 // tiles.  Each wave runs an online softmax over its keys, two tiles of loads
 // ahead of the one it scores (running max raised only when a tile's max exceeds
 // it by 2^8, so the common tile costs no rescale); the waves are combined

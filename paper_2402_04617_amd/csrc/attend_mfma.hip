@@ -78,8 +78,11 @@ __device__ __forceinline__ int tile_off(int r, int g) { return r * D + 8 * (g ^ 
 
 constexpr int NBUF = 4;         // K and V tile buffers: a pair of tiles in use, the next pair in flight
 constexpr float kMaskCost = 1.5f;  // cost of a masked tile, in plain tiles
-constexpr float kSelTiles = 1.f;  // the in-prologue unit selection, in plain tiles
-constexpr float kSelTilesLong = 2.f;  // the same for rows of more than kFusedSelectShort units
+// The in-prologue unit selection, in plain tiles.  Rows of at most 1,024 units: 0.5, 1, 1.5 and 2
+// tiles make a 128K chunk 90.1, 89.3, 89.2 and 90.2 us, a 389-query chunk at 32K 62.1, 63.1,
+// 62.0 and 62.0, four sequences of 24 tokens 44.4, 44.0, 44.7 and 44.7, 256 tokens at 64K 55.9,
+// 56.0, 57.1 and 57.4; longer rows: 1, 2 and 3 tiles make 512 tokens at 1M 94.3, 95.5 and 96.9.
+constexpr float kSelTiles = 1.f;
 constexpr int kRowTable = 4096;  // key-group positions kept in LDS (512 tiles of 8-key groups, 64 of single keys)
 constexpr int kSelLds = 1024;    // lookup entries kept in LDS
 static_assert(kFusedSelectMaxK <= kSelLds, "a selected lookup row fits in LDS");
@@ -125,9 +128,11 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
   __shared__ __attribute__((aligned(256))) Smem<D> sm;
 
   // The prologue is latency: 10 us for a selecting workgroup and 6.7 for another of a
-  // 128K step's 79, now 7.4 and 4.7 of 71 (arguments, divisions and the part bounds
-  // 1.8 -> 0.9; selection 4.6 -> 2.9; the queries and K(t0) load while the position
-  // table is filled).
+  // 128K step's 79, 7.4 and 4.7 since (arguments, divisions and the part bounds
+  // 1.8 -> 0.9; selection 4.6 -> 2.9; the queries and K(t0) are requested before the
+  // position table is filled).  In a workgroup whose tiles hold units the table does not
+  // hide them: a lookup entry lies in LDS or in memory and is read through one pointer,
+  // and that read waits for every load in flight.
   // Every argument the prologue reads, requested at once: read where they are used,
   // their cold cache lines were waited for one after another.
   asm volatile("" ::"s"(a.batch), "s"(a.capacity), "s"(a.q_head_stride), "s"(a.q), "s"(a.k_store), "s"(a.v_store),
@@ -190,7 +195,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
     if (geo.n_sel > 0 && geo.n_sel < geo.n_units) {
       const int u_end = (geo.n_init + geo.n_sel * geo.block_size + KB - 1) / KB;
       s_end = min(max(u_end, rt0), a_m);
-      c_seltile += (SEL > 2 ? kSelTilesLong : kSelTiles) * (float)rparts * __builtin_amdgcn_rcpf((float)max(1, rt1 - rt0));
+      c_seltile += kSelTiles * (float)rparts * __builtin_amdgcn_rcpf((float)max(1, rt1 - rt0));
     }
   }
   const float c_sel = c_seltile * (float)(s_end - rt0), c_plain = c_sel + (float)(a_m - s_end);
@@ -892,7 +897,7 @@ __global__ void __launch_bounds__(64 * NWAVE, 1) attend_mfma_kernel(AttendArgs a
 
   if (t_begin < t_end) {
     // K(t0) needs no table: its rows' positions directly, so that the load is on its
-    // way before the table is filled.
+    // way before the table is filled (where no unit is read: see above).
     TileOff off0, off1;
     {
       uint32_t e0[NI];

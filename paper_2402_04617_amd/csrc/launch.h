@@ -156,9 +156,9 @@ constexpr int kDecodeSelMax = 1024;
 constexpr int kWaveSelMaxK = 48;
 
 // Score rows the matrix-core attention selects from itself: rows of at most
-// kFusedSelectShort units hold two keys per thread, longer rows up to
-// kFusedSelectMax sixteen (filtered first); at most kFusedSelectMaxK units are
-// looked up.
+// kFusedSelectShort units by one wave (up to kWaveSelMaxK of them) or with two keys per
+// thread of all eight, longer rows up to kFusedSelectMax with sixteen; at most
+// kFusedSelectMaxK units are looked up.
 constexpr int kFusedSelectShort = 1024;
 constexpr int kFusedSelectMax = 8192;
 constexpr int kFusedSelectMaxK = 1024;

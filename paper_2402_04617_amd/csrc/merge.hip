@@ -5,8 +5,8 @@
 // One thread per (row, 16 bytes of partial row): 8 dims of a scaled-fp16 partial
 // (bfloat16 inputs; value * 2^exp[row] restores the row) or 4 dims of a float32
 // one.  A thread takes all parts, CH at a time (CH = the part count, or 8), every load
-// of those issued before the first use.  More than 8 parts of few rows (decoding): a
-// workgroup per row, its threads split into groups that take every GR-th part and are
+// of those issued before the first use.  More than 8 parts of few rows (decoding), at
+// least half as many as a workgroup has groups: a workgroup per row, its threads split into groups that take every GR-th part and are
 // joined in LDS -- the parts are then the only parallelism (25 parts of 32 rows: 6.8 us
 // one thread per piece, 4.3 split; 16 parts of 2,048 rows: 3.7 and 6.5).
 #include "launch.h"
