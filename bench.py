@@ -39,26 +39,26 @@ PEAK_HBM_GBS = 8000.0
 # moved by the plain copy of `bench.py --copy-calibration 1024`.  An entry holds for the kernel
 # sources it was taken on (sha256 of each file); it is reported as null once any of them changes.
 CSRC = os.path.join(ROOT, "paper_2402_04617_amd", "csrc")
-COPY_FETCH = 524300.0 / 1048576.0  # FETCH_SIZE KiB per KiB read by the copy
+COPY_FETCH = 524297.7 / 1048576.0  # FETCH_SIZE KiB per KiB read by the copy
 COPY_WRITE = 1048576.0 / 1048576.0  # WRITE_SIZE KiB per KiB written by the copy
 KERNEL_TRAFFIC = {
     # key: {"src": {file: sha256}, "fetch_kib": ..., "write_kib": ...}, per launch (per call for
     # infllm_score_units: its two kernels), from `rocprofv3 --pmc FETCH_SIZE` and `--pmc WRITE_SIZE`
     # runs of `bench.py --legs 1m,decode --no-cpu-baseline --steps 1 --warmup 0`, averaged over the
     # replayed launches the bench line times
-    "attend_mfma_llama3-8b-128k": {"src": {"attend_mfma.hip": "8e6f615f1b8b0f3845348431fc7e85216df7b7ee1dd5f879cd23492c919980f7", "launch.h": "773b89a4b862e0906d83400bc662d292d0f41bae789623c3fb8b00f10acda697"},
-                                   "fetch_kib": 20095.6, "write_kib": 16896.0},
-    "score_llama3-8b-128k": {"src": {"score.hip": "b863ba9bf6e01b4901383469e615c02c7ae9b482693bef88e3f29735e4666a13", "launch.h": "773b89a4b862e0906d83400bc662d292d0f41bae789623c3fb8b00f10acda697"},
+    "attend_mfma_llama3-8b-128k": {"src": {"attend_mfma.hip": "d65aae73a919edc4e0075719e69771e6eb703ad3ba576a1de6a04e88c50d2423", "launch.h": "c84efff6ce119de53c6f3069382c05bae80fbc2fe80d6542be7f1e705e4441e6"},
+                                   "fetch_kib": 20577.8, "write_kib": 16896.0},
+    "score_llama3-8b-128k": {"src": {"score.hip": "b863ba9bf6e01b4901383469e615c02c7ae9b482693bef88e3f29735e4666a13", "launch.h": "c84efff6ce119de53c6f3069382c05bae80fbc2fe80d6542be7f1e705e4441e6"},
                              "fetch_kib": 2086.6 + 2281.5, "write_kib": 64.0 + 34.3},
-    "append_llama3-8b-128k": {"src": {"append.hip": "d09c349a86c28dba43f0fcae0b6c8675a8486c7e054e0404c7a79a8b140f5002", "launch.h": "773b89a4b862e0906d83400bc662d292d0f41bae789623c3fb8b00f10acda697"},
-                              "fetch_kib": 5717.6, "write_kib": 6659.0},
-    "score_llama3-8b-1m": {"src": {"score.hip": "b863ba9bf6e01b4901383469e615c02c7ae9b482693bef88e3f29735e4666a13", "launch.h": "773b89a4b862e0906d83400bc662d292d0f41bae789623c3fb8b00f10acda697"},
+    "append_llama3-8b-128k": {"src": {"append.hip": "0837574dfd5863477c3058538a7d7226d7cbcb94eced149826ff5f829db011cc", "launch.h": "c84efff6ce119de53c6f3069382c05bae80fbc2fe80d6542be7f1e705e4441e6"},
+                              "fetch_kib": 5737.5, "write_kib": 6659.0},
+    "score_llama3-8b-1m": {"src": {"score.hip": "b863ba9bf6e01b4901383469e615c02c7ae9b482693bef88e3f29735e4666a13", "launch.h": "c84efff6ce119de53c6f3069382c05bae80fbc2fe80d6542be7f1e705e4441e6"},
                            "fetch_kib": 2086.5 + 16617.6, "write_kib": 64.0 + 282.8},
-    "append_llama3-8b-1m": {"src": {"append.hip": "d09c349a86c28dba43f0fcae0b6c8675a8486c7e054e0404c7a79a8b140f5002", "launch.h": "773b89a4b862e0906d83400bc662d292d0f41bae789623c3fb8b00f10acda697"},
-                            "fetch_kib": 5717.6, "write_kib": 6659.0},
-    "attend_decode": {"src": {"attend_decode.hip": "e9c010e0b521a9e279ded2a3f90fe08bc8e43dc66eb5d0d9b4d86bcbdbd07953", "launch.h": "773b89a4b862e0906d83400bc662d292d0f41bae789623c3fb8b00f10acda697"},
-                      "fetch_kib": 270891.2, "write_kib": 544.1},
-    "score_decode": {"src": {"score.hip": "b863ba9bf6e01b4901383469e615c02c7ae9b482693bef88e3f29735e4666a13", "launch.h": "773b89a4b862e0906d83400bc662d292d0f41bae789623c3fb8b00f10acda697"},
+    "append_llama3-8b-1m": {"src": {"append.hip": "0837574dfd5863477c3058538a7d7226d7cbcb94eced149826ff5f829db011cc", "launch.h": "c84efff6ce119de53c6f3069382c05bae80fbc2fe80d6542be7f1e705e4441e6"},
+                            "fetch_kib": 5737.6, "write_kib": 6659.0},
+    "attend_decode": {"src": {"attend_decode.hip": "7dd436b89093127ccc35eccd9390051f091b6c75e676d39fe4353bdd49fcd4ac", "launch.h": "c84efff6ce119de53c6f3069382c05bae80fbc2fe80d6542be7f1e705e4441e6"},
+                      "fetch_kib": 270950.8, "write_kib": 544.1},
+    "score_decode": {"src": {"score.hip": "b863ba9bf6e01b4901383469e615c02c7ae9b482693bef88e3f29735e4666a13", "launch.h": "c84efff6ce119de53c6f3069382c05bae80fbc2fe80d6542be7f1e705e4441e6"},
                      "fetch_kib": 102.5 + 32281.5, "write_kib": 64.0 + 496.0},
 }
 

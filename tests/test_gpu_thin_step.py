@@ -79,9 +79,14 @@ def test_thin_step(case, ties):
     out2, lse2 = torch.zeros_like(out), torch.zeros_like(lse)
     F.infllm_chunk_attend(p, L2.mem.struct, q, n_q * D, n_q, past, idx, k, out2, n_q * D, lse2, L2.ws)
     torch.cuda.synchronize()
-    # the same kernel on the same lookup, but perhaps another split of the keys
-    assert float((out.float() - out2.float()).abs().max()) <= (3e-2 if dtype == "bf16" else 1e-5)
-    assert float((lse - lse2).abs().max()) <= (1e-2 if mode == "remap" else 1e-3)
+    if dtype == "f32" or (n_q == 1 and G in (1, 2, 4, 8)):
+        # the same kernel, lookup and parts
+        assert torch.equal(out, out2) and torch.equal(lse, lse2)
+    else:
+        # the matrix-core kernel splits the keys elsewhere when it selects: bf16 probabilities against another
+        # maximum (2^-9 each), fp16 partials, a bf16 result
+        assert float((out.float() - out2.float()).abs().max()) <= 1e-2 * float(out2.float().abs().max())
+        assert float((lse - lse2).abs().max()) <= 1e-3
 
 
 @pytest.mark.parametrize("n_q", [1, 4])
@@ -118,7 +123,8 @@ def test_thin_step_varlen(n_q):
         assert torch.equal(i1[0], idx[b])
         if units[b]:
             assert torch.equal(s1, scores[b, :, :units[b]])
-        assert float((o1[0].float() - out[b].float()).abs().max()) <= 3e-2
+        # another part count than the batch's: partial rows of 11 bits, results of 8 (and as above)
+        assert float((o1[0].float() - out[b].float()).abs().max()) <= 1e-2 * float(o1.float().abs().max())
         assert float((l1[0] - lse[b]).abs().max()) <= 1e-3
 
 
