@@ -3,6 +3,8 @@
 //  - attend_f32_kernel: float32 inputs (any n_q), float32 matrix cores, expf online
 //    softmax; the float32 accuracy path.  It reads keys through the same
 //    virtual key axis as the other kernels.
+#include <algorithm>
+
 #include "launch.h"
 
 namespace infllm {
@@ -351,7 +353,7 @@ bool decode_eligible(bool bf16, int n_q, int G, int n_sel) {
 
 // Most key parts of the decode kernel: of kDecodeMinWork keys * head_dim each.
 static int decode_most_parts(int head_dim, int64_t n_virtual) {
-  return (int)max((int64_t)1, min((int64_t)kDecodeTargetWgs, n_virtual * head_dim / kDecodeMinWork));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kDecodeTargetWgs, n_virtual * head_dim / kDecodeMinWork));
 }
 
 // Key parts of the decode kernel: a short context whole, else the cheapest of the counts
@@ -370,16 +372,16 @@ int attend_decode_parts(int bh, int G, int head_dim, int n_virtual) {
   // 200 as 400; of 1,100 keys 45 and 42)
   const int pass = (kDecodeTargetWgs + bh - 1) / bh;
   if (bh > kDecodeTargetWgs / 2 || (3 * bh > kDecodeTargetWgs && n_virtual >= 4096))
-    return max(1, min(pass, n_virtual / 256));
+    return std::max(1, std::min(pass, n_virtual / 256));
   const int fit2 = kDecodeTargetWgs / bh, fit1 = kDecodeTargetWgs / 2 / bh;
   const int tile = decode_step_keys(head_dim);  // of all waves
   int best = 1, best_cost = 0;
   for (const int c : {1, 8, 16, fit1, fit2}) {
-    int p = min(c, min(fit2, most));
+    int p = std::min(c, std::min(fit2, most));
     const int tiles = (n_virtual + p * tile - 1) / (p * tile);
     const bool few = tiles <= kDecodeShortTiles;
     // (no more for two workgroups per unit than fill the buffers of their waves)
-    if (few && p > fit1) p = max(fit1, (n_virtual + kDecodeShortTiles * tile - 1) / (kDecodeShortTiles * tile));
+    if (few && p > fit1) p = std::max(fit1, (n_virtual + kDecodeShortTiles * tile - 1) / (kDecodeShortTiles * tile));
     const int padded = few ? kDecodeShortTiles : (tiles + 2) / 3 * 3;
     const int rounds = (bh * p + kDecodeTargetWgs / 2 - 1) / (kDecodeTargetWgs / 2);
     const int cost = 28 * rounds + 4 * padded + (int)((int64_t)4 * n_virtual / (p * tile)) + (p > 1 ? 24 : 0) +
@@ -397,11 +399,11 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
   *row_waves = kMfmaWaves;
   const int G = n_q_heads / n_kv_heads;
   if (decode_eligible(bf16, n_q, G, n_sel))
-    return min(attend_decode_parts(batch * n_kv_heads, G, head_dim, n_virtual), max(1, max_parts));
+    return std::min(attend_decode_parts(batch * n_kv_heads, G, head_dim, n_virtual), std::max(1, max_parts));
   const int R = G * n_q;
   const int key_tile = bf16 ? 64 : kF32Keys;
   const int n_tiles = (n_virtual + key_tile - 1) / key_tile;
-  const int cap = min(bf16 ? 8 : 16, min(max(1, n_tiles / 2), max(1, max_parts)));
+  const int cap = std::min(bf16 ? 8 : 16, std::min(std::max(1, n_tiles / 2), std::max(1, max_parts)));
   // Both kernels put one wave on a SIMD's matrix core (float32) or eight on a compute
   // unit's (bf16) at a time, so a part count that starts a new round of workgroups for a few of
   // them is worse than a lower one.  A workgroup costs its tiles plus kPartCost (prologue and
@@ -432,9 +434,9 @@ int attend_choose_parts(bool bf16, int batch, int n_q_heads, int n_kv_heads, int
       auto wg_cost = [&](int64_t tiles) { return 4 * kPartCost + (tile_cost * tiles + p - 1) / p; };
       int64_t cost = rounds * wg_cost(n_tiles) + (p > 1 ? 4 * kMergeCost : 0);
       if (p == 1 && rounds > 1) {
-        const int64_t after = max((int64_t)0, wgs - rounds * per_round / 2);  // workgroups after the middle one
+        const int64_t after = std::max((int64_t)0, wgs - rounds * per_round / 2);  // workgroups after the middle one
         const int64_t mid_tiles = (n_virtual - n_q + n_q * after / wgs) / key_tile + 1;
-        cost = max(wg_cost(n_tiles), rounds * wg_cost(min((int64_t)n_tiles, mid_tiles)));
+        cost = std::max(wg_cost(n_tiles), rounds * wg_cost(std::min((int64_t)n_tiles, mid_tiles)));
       }
       if ((half == 0 && p == 1) || cost < best_cost) {
         best = p;
